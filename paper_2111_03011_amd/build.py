@@ -9,6 +9,7 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -50,16 +51,18 @@ def build(verbose: bool = False) -> str:
     hipcc = _hipcc()
     os.makedirs(BUILD_DIR, exist_ok=True)
     inc = ["-I", INCLUDE, "-I", CSRC]
-    objs = []
-    for src in ("kernels.hip", "noalloc.hip", "tnc.cpp"):
+    objs, jobs = [], []
+    for src in ("kernels.hip", "gemm_planes.hip", "noalloc.hip", "tnc.cpp"):
         obj = os.path.join(BUILD_DIR, src.replace(".", "_") + ".o")
         path = os.path.join(CSRC, src)
         if src.endswith(".hip"):
             cmd = [hipcc, *HIP_FLAGS, *inc, "-c", path, "-o", obj]
         else:
             cmd = [hipcc, *HOST_FLAGS, *inc, "-D__HIP_PLATFORM_AMD__", "-c", path, "-o", obj]
-        _run(cmd, verbose)
+        jobs.append(cmd)
         objs.append(obj)
+    with ThreadPoolExecutor(max_workers=4) as pool:      # hipcc processes; one per file
+        list(pool.map(lambda c: _run(c, verbose), jobs))
     tmp = LIB + ".tmp"
     _run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", tmp], verbose)
     os.replace(tmp, LIB)

@@ -17,95 +17,13 @@
 
 #include <cstdlib>
 
+#include "device_util.h"
+
 namespace tnc {
 
 namespace {
 
 constexpr int kThreads = 256;
-
-// Fold per-lane maxima m >= 0 into the kAmaxSlots slots of record copy `slice`,
-// amax[slice * step + j], with atomic maxima on the float bits (non-negative floats order
-// like their bits); the slot is a hash of the workgroup index, which spreads the atomics of
-// a large output over many addresses, and readers take the maximum over the slots
-// (amax_read).  Every lane of the wave calls this; a lane without an element passes
-// slice = -1.  When the lanes with an element share one slice the wave reduces first and
-// issues one atomic.
-__device__ __forceinline__ void amax_commit(float m, int64_t slice, uint32_t* amax, int64_t step) {
-  amax += (blockIdx.x + 7u * blockIdx.y + 13u * blockIdx.z) & (kAmaxSlots - 1);
-  int64_t s0 = slice;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const int64_t o = __shfl_xor(s0, off);
-    s0 = s0 > o ? s0 : o;
-  }
-  if (s0 < 0) return;
-  if (__all(slice == s0 || slice < 0)) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    if ((threadIdx.x & 63) == 0 && m > 0.f) atomicMax(amax + s0 * step, __float_as_uint(m));
-  } else if (slice >= 0 && m > 0.f) {
-    atomicMax(amax + slice * step, __float_as_uint(m));
-  }
-}
-
-// maximum over a record's kAmaxSlots slots (lane j reads slots j, j + 64, ...; every lane
-// of the wave gets the result)
-__device__ __forceinline__ uint32_t amax_read(const uint32_t* slots) {
-  const int lane = threadIdx.x & 63;
-  uint32_t v = 0;
-#pragma unroll
-  for (int k = 0; k < kAmaxSlots / 64; ++k) {
-    const uint32_t o = slots[lane + 64 * k];
-    v = v > o ? v : o;
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const uint32_t o = __shfl_xor(v, off);
-    v = v > o ? v : o;
-  }
-  return v;
-}
-
-// amax_commit for a workgroup whose lanes all hold elements of one slice: the four waves'
-// maxima meet in LDS and one atomic maximum goes out per workgroup.  Every thread of the
-// workgroup calls it (it synchronises the workgroup).
-__device__ __forceinline__ void amax_commit_wg(float m, int64_t slice, uint32_t* amax, int64_t step) {
-  __shared__ float red[16];   // up to 16 waves per workgroup
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float w = red[0];
-    for (int i = 1; i < int(blockDim.x >> 6); ++i) w = fmaxf(w, red[i]);
-    if (w > 0.f)
-      atomicMax(amax + slice * step + ((blockIdx.x + 7u * blockIdx.y + 13u * blockIdx.z) & (kAmaxSlots - 1)),
-                __float_as_uint(w));
-  }
-}
-
-// Scale shift of an operand from its largest component (float bits): the FP32 forms
-// (f16 = false) leave operands whose largest component lies in [2^-20, 2^21) alone and
-// bring the others to [1, 2); the FP16 form brings it to [2^13, 2^14) (exponents clamped
-// to [-110, 127]).  An all-zero operand is not scaled.  The result lies in [-126, 127].
-__device__ __forceinline__ int rec_shift(uint32_t amax_bits, bool f16) {
-  const int e = int((amax_bits >> 23) & 0xffu) - 127;   // -127 for zero and subnormals
-  if (f16) return 13 - (e < -110 ? -110 : e);
-  if (amax_bits == 0u || (e >= -20 && e <= 20)) return 0;
-  return e > 126 ? -126 : -e;
-}
-
-// 2^k for k in [-126, 127]
-__device__ __forceinline__ float pow2f(int k) { return __uint_as_float(uint32_t(127 + k) << 23); }
-
-// Shift and exponent of record copy `slice` (every lane of the wave calls it).
-__device__ __forceinline__ void rec_load(const uint32_t* rec, int64_t step, int64_t slice, bool f16,
-                                         int& shift, int& expo) {
-  const uint32_t* r = rec + slice * step;
-  shift = rec_shift(amax_read(r), f16);
-  expo = int(r[kRecExp]);
-}
-
 
 // ---------------------------------------------------------------------------------
 // big x small stream: the small operand S (one copy shared by every row and slice) sits in
@@ -295,35 +213,6 @@ __global__ __launch_bounds__(kThreads) void k_stream_rows(StreamArgs a, int rw, 
 
 // ---------------------------------------------------------------------------------
 // complex64 GEMM on v_mfma_f32_32x32x2f32
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2v __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ int64_t xcd_remap(int64_t bid, int64_t nb) {
-  // Workgroups are dealt to the 8 XCDs round-robin; renumber them so that each XCD
-  // receives a contiguous range of tiles (neighbouring tiles share operand panels,
-  // which then stay in that XCD's L2).
-  const int64_t q = nb / 8, rem = nb % 8, x = bid % 8;
-  return x * q + (x < rem ? x : rem) + bid / 8;
-}
-
-// Scatter the low `nbits` bits of x to the bit positions pos[0..nbits) (a software pdep).
-// Unrolled to MAXB >= nbits iterations so that pos[] is read at constant offsets (scalar
-// loads from the kernel arguments) instead of through a dynamically indexed array.
-template <int MAXB>
-__device__ __forceinline__ int64_t scatter_u(int64_t x, const int8_t* pos, int nbits) {
-  int64_t o = 0;
-#pragma unroll
-  for (int j = 0; j < MAXB; ++j)
-    if (j < nbits) o += ((x >> j) & 1) << pos[j];
-  return o;
-}
-
-__device__ __forceinline__ float2 keep_if(float2 v, uint32_t mask) {
-  uint2 u = __builtin_bit_cast(uint2, v);
-  u.x &= mask;
-  u.y &= mask;
-  return __builtin_bit_cast(float2, u);
-}
 
 // Tile bookkeeping shared by the GEMM kernels: which output tile, slice, row and K range
 // this workgroup owns, the operand bases of the tile corner, and for every load slot of
@@ -337,18 +226,6 @@ __device__ __forceinline__ float2 keep_if(float2 v, uint32_t mask) {
 // in LDS (LDS_TAB) or one entry per lane in registers, read with readlane.  Offsets within
 // one operand row fit in 31 bits (also checked when the plan is compiled).
 constexpr int kKLevels = 4;
-
-// Operand scales of a GEMM for slice copy sl from the records of A and B; the workgroup
-// that owns the slice's first tile (`writer`) records C's exponent.
-__device__ __forceinline__ void rec_scales(const GemmArgs& a, int64_t sl, bool f16, bool writer,
-                                           float& sa, float& sb) {
-  int sha, shb, ea, eb;
-  rec_load(a.rec_a, a.rec_a_step, sl, f16, sha, ea);
-  rec_load(a.rec_b, a.rec_b_step, sl, f16, shb, eb);
-  sa = pow2f(sha);
-  sb = pow2f(shb);
-  if (writer && threadIdx.x == 0) a.rec_c[sl * a.rec_c_step + kRecExp] = uint32_t(ea + eb - sha - shb);
-}
 
 template <int BM, int BN, int BK, bool A_MFAST, bool B_NFAST, bool LDS_TAB, int NT = kThreads>
 struct GemmTile {
@@ -639,9 +516,9 @@ struct GemmTile {
 };
 
 template <int WAVES_M, int WAVES_N, int UM, int UN, int BK, bool A_MFAST, bool B_NFAST>
-__global__ __launch_bounds__(WAVES_M * WAVES_N * 64) __attribute__((amdgpu_waves_per_eu(WAVES_M * WAVES_N == 4 ? 3 : 2))) void k_gemm(GemmArgs a) {
-  constexpr int NT = WAVES_M * WAVES_N * 64;   // four or eight waves
-  static_assert(NT == 256 || NT == 512, "four or eight waves per workgroup");
+__global__ __launch_bounds__(WAVES_M * WAVES_N * 64) __attribute__((amdgpu_waves_per_eu(3))) void k_gemm(GemmArgs a) {
+  constexpr int NT = WAVES_M * WAVES_N * 64;
+  static_assert(NT == 256, "four waves per workgroup");
   constexpr int BM = WAVES_M * UM * 32;
   constexpr int BN = WAVES_N * UN * 16;
   using Tile = GemmTile<BM, BN, BK, A_MFAST, B_NFAST, true, NT>;
@@ -1211,8 +1088,8 @@ __device__ __forceinline__ void split_pair(float2 x, uint32_t& hi, uint32_t& lo)
 template <int WAVES_M, int WAVES_N, int UM, int UN, bool A_MFAST, bool B_NFAST, int MODE>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void k_gemm_bf16x3(GemmArgs a) {
   constexpr bool F16 = (MODE == 2);
-  constexpr int NT = WAVES_M * WAVES_N * 64;   // four or eight waves
-  static_assert(NT == 256 || NT == 512, "four or eight waves per workgroup");
+  constexpr int NT = WAVES_M * WAVES_N * 64;
+  static_assert(NT == 256, "four waves per workgroup");
   constexpr int BK = 16;                       // complex k per LDS stage (two MFMA steps)
   constexpr int BM = WAVES_M * UM * 32;
   constexpr int BN = WAVES_N * UN * 16;
@@ -1830,7 +1707,8 @@ hipError_t launch_stream(const StreamArgs& a, hipStream_t s) {
 // 1 = 128 x 16 (4x1 waves, one MFMA tile each), 2 = 64 x 32 (2x2 waves, one tile each),
 // 3 = 128 x 128 (2x2 waves, 2x4 MFMA tiles each), 4 = 128 x 32 (4x1 waves, 1x2 tiles each),
 // 5 = 128 x 8 on 16x16x4 MFMA tiles (complex64 only; split precision uses 1), or, for rows
-// of narrow long-K products, k_gemm_rows_narrow in every form.
+// of narrow long-K products, k_gemm_rows_narrow in every form; 7 = 256 x 128 and 8 = 128 x 64 on
+// the 16-bit matrix cores in every form (gemm_planes.hip).
 template <int MH, int NN>
 hipError_t launch_rows_narrow_t(const GemmArgs& a, hipStream_t s) {
   const int64_t waves = a.rows * a.nb, blocks = (waves + 3) / 4;
@@ -1932,54 +1810,9 @@ hipError_t launch_gemm_outer(const GemmArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-// Configurations 7 and 8: eight-wave workgroups, each wave with the 2 x 2 matrix-core
-// tiles of configuration 0, so one workgroup covers 128 x 128 (7) or 256 x 64 (8) complex
-// outputs and every staged operand byte feeds more matrix instructions than with 128 x 64;
-// split precision (96 or 80 KB of LDS per workgroup) and complex64 (k_gemm with eight
-// waves, 68 or 86 KB); no row stacking.
-template <int WM, int WN>
-hipError_t launch_gemm_split_big_t(const GemmArgs& a, hipStream_t s) {
-  constexpr int UM = 2, UN = 2;
-  constexpr int BM = WM * UM * 32, BN = WN * UN * 16;
-  const int64_t tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  const int64_t zs = a.rows * a.nb * a.k_splits;
-  const int64_t gy = zs < 65535 ? zs : 65535;
-  const int64_t gz = (zs + gy - 1) / gy;
-  const dim3 grid{unsigned(tiles), unsigned(gy), unsigned(gz)};
-  const int sel = (a.a_mfast ? 1 : 0) | (a.b_nfast ? 2 : 0);
-  if (a.precision == 0) {      // complex64: the FP32 kernel with eight waves
-    switch (sel) {
-      case 0: hipLaunchKernelGGL((k_gemm<WM, WN, UM, UN, 16, false, false>), grid, dim3(WM * WN * 64), 0, s, a); break;
-      case 1: hipLaunchKernelGGL((k_gemm<WM, WN, UM, UN, 16, true, false>), grid, dim3(WM * WN * 64), 0, s, a); break;
-      case 2: hipLaunchKernelGGL((k_gemm<WM, WN, UM, UN, 16, false, true>), grid, dim3(WM * WN * 64), 0, s, a); break;
-      default: hipLaunchKernelGGL((k_gemm<WM, WN, UM, UN, 16, true, true>), grid, dim3(WM * WN * 64), 0, s, a); break;
-    }
-    return hipGetLastError();
-  }
-  const int mode = a.precision == 1 ? 0 : 2;
-  switch (sel * 3 + mode) {
-#define TNC_BIG_CASE(S, MD, AF, BF)                                                            \
-  case S * 3 + MD:                                                                            \
-    hipLaunchKernelGGL((k_gemm_bf16x3<WM, WN, UM, UN, AF, BF, MD>), grid, dim3(WM * WN * 64), 0, s, a); \
-    break;
-    TNC_BIG_CASE(0, 0, false, false) TNC_BIG_CASE(0, 2, false, false)
-    TNC_BIG_CASE(1, 0, true, false) TNC_BIG_CASE(1, 2, true, false)
-    TNC_BIG_CASE(2, 0, false, true) TNC_BIG_CASE(2, 2, false, true)
-    TNC_BIG_CASE(3, 0, true, true) TNC_BIG_CASE(3, 2, true, true)
-#undef TNC_BIG_CASE
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_gemm_split_big(const GemmArgs& a, hipStream_t s) {
-  if (a.stk || (a.precision != 0 && a.precision != 1 && a.precision != 3)) return hipErrorInvalidValue;
-  return a.config == 7 ? launch_gemm_split_big_t<2, 4>(a, s) : launch_gemm_split_big_t<4, 2>(a, s);
-}
-
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.config == 6) return launch_gemm_outer(a, s);
-  if (a.config == 7 || a.config == 8) return launch_gemm_split_big(a, s);
+  if (a.config == 7 || a.config == 8) return launch_gemm_planes(a, s);
   if (a.config == 5) {
     if (a.precision == 0 || rows_narrow_fits(a)) return launch_gemm_n8(a, s);
     GemmArgs b = a;            // the split-precision kernels have no 8-wide tile

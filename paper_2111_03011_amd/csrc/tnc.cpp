@@ -132,12 +132,14 @@ struct Launch {
   int b_in0 = -1, b_in1 = -1, b_out = -1, b_tmp = -1;
   int64_t g0 = -1, g1 = -1;   // byte offsets of row gathers in the constants block
   int64_t stk_off = -1, perm_off = -1;   // row-stacking tables (GEMM), same block
+  int64_t ktab_off = -1, mtab_off = -1, ntab_off = -1;   // tile offset tables (GEMM), same block
   int rec_in0 = -1, rec_in1 = -1, rec_out = -1;   // scale records of the operands and result
   bool shared = false;        // slice-dependent, but the same for every slice of a batch
   int split_op = 0;                      // K_SPLIT: SPLIT_ZERO
   int64_t n_elems = 0;        // words per slice copy (record clearing)
   bool enabled = true;        // a split-K reduction is switched off when tuning drops split-K
   int max_splits = 1;         // split-K factor the partial buffer was sized for
+  bool planes = false;        // planned on a plane kernel (GEMM)
   StreamArgs st{};
   GemmArgs gm{};
   ReduceArgs rd{};
@@ -260,6 +262,7 @@ struct Compiler {
   std::vector<TState> T;
   std::set<int32_t> sliced_set;
   std::map<int32_t, int> sliced_bit;
+  bool finite = true;           // every leaf entry is
 
   Compiler(tnc_net_s& n, tnc_plan_s& p) : net(n), plan(p) {}
 
@@ -364,7 +367,10 @@ struct Compiler {
       }
       s.dense = dense;
       float mx = 0.f;
-      for (float v : host) mx = std::max(mx, std::fabs(v));
+      for (float v : host) {
+        mx = std::max(mx, std::fabs(v));
+        finite = finite && std::isfinite(v);
+      }
       uint32_t bits;
       std::memcpy(&bits, &mx, 4);
       s.rec = new_rec(REC_CONST, false);
@@ -470,8 +476,8 @@ struct Compiler {
   // Estimated fraction of the MFMA tile work that is useful, for P on the M side
   static double tile_fill(const TState& P, const TState& Q, const TState& C, int nm, int nn) {
     const int64_t M = int64_t(1) << nm, N = int64_t(1) << nn, rows = C.rows();
-    static const int64_t kBM[kConfigs] = {128, 128, 64, 128, 128, 128, 256, 128, 256};
-    static const int64_t kBN[kConfigs] = {64, 16, 32, 128, 32, 8, 512, 128, 64};
+    static const int64_t kBM[kConfigs] = {128, 128, 64, 128, 128, 128, 256, 128, 128};
+    static const int64_t kBN[kConfigs] = {64, 16, 32, 128, 32, 8, 512, 64, 64};
     int64_t m_eff = M;
     if (rows > 1 && Q.rows() == 1 && P.q == C.q && M >= 128) m_eff = M * rows;
     double fm;
@@ -487,20 +493,28 @@ struct Compiler {
     return fm * std::min(1.0, double(N) / double(kBN[cfg_n]));
   }
 
-  // GEMM tile configurations (see launch_gemm); 6 is the short-K vector kernel, 7 and 8
-  // the eight-wave 128 x 128 and 256 x 64 tiles of the split-precision forms
+  // GEMM tile configurations (see launch_gemm); 6 is the short-K vector kernel, 7 and 8 the
+  // plane kernels, counted as 128 x 64 tiles for split-K, whichever size a launch takes
   static constexpr int kConfigs = 9;
 
   // read at every plan compile, so that one process can build plans both ways
   static bool stacking_enabled() { return std::getenv("TNC_NO_STACK") == nullptr; }
 
-  // the short-K kernel (configuration 6) takes K <= 16 without row stacking; the eight-wave
-  // tiles (configurations 7, 8) any precision without row stacking
+  // the short-K kernel (configuration 6) takes K <= 16 without row stacking; for the
+  // plane kernels see planes_ok
   static bool outer_ok(const GemmArgs& g, bool stacked) { return g.nk <= 4 && !stacked; }
-  static bool big_ok(const GemmArgs& g, bool stacked) { (void)g; return !stacked; }
+
+  // The plane kernels (configurations 7 and 8): K of at least two of their 16-k tiles, 32-bit byte
+  // offsets inside an operand row, tile tables of bounded size, no row stacking, a 128-row tile
+  // inside one folded row; and finite leaves, since the split of an infinity is infinity and NaN.
+  static bool planes_ok(const GemmArgs& g, bool stacked, int64_t M, int64_t N, int rank_a, int rank_b,
+                        bool finite) {
+    return finite && !stacked && g.nk >= 5 && g.nk <= 20 && rank_a <= 29 && rank_b <= 29 &&
+           M <= (int64_t(1) << 23) && N <= (int64_t(1) << 22) && (!g.fold || g.nm >= 7);
+  }
 
   static void choose_tiles(GemmArgs& g, int64_t M, int64_t N, int64_t Kd, int64_t rows,
-                           bool stacked) {
+                           bool stacked, bool planes, bool inv) {
     static const int group = std::getenv("TNC_GEMM_GROUP") ? std::atoi(std::getenv("TNC_GEMM_GROUP")) : 4;
     g.group_m = group;
     const char* force = std::getenv("TNC_GEMM_CONFIG");
@@ -510,19 +524,26 @@ struct Compiler {
     // short contraction, wide output of at least 2^22 elements: bound by writing C
     if (outer_ok(g, stacked) && N >= 64 && double(M) * double(N) * double(rows) >= 4194304.0)
       g.config = 6;
+    // K >= 32, at least one whole 128 x 64 tile: the 16-bit matrix cores in every form
+    if (planes && M >= 128 && N >= 64) g.config = (M >= 256 && N >= 128) ? 7 : 8;
     if (force) {
       const int f = std::min(kConfigs - 1, std::max(0, std::atoi(force)));
-      if ((f != 6 || outer_ok(g, stacked)) && (f < 7 || big_ok(g, stacked))) g.config = f;
+      if ((f != 6 || outer_ok(g, stacked)) && (f < 7 || planes)) g.config = f;
     }
-    static const int64_t kBM[kConfigs] = {128, 128, 64, 128, 128, 128, 256, 128, 256};
-    static const int64_t kBN[kConfigs] = {64, 16, 32, 128, 32, 8, 512, 128, 64};
+    static const int64_t kBM[kConfigs] = {128, 128, 64, 128, 128, 128, 256, 128, 128};
+    static const int64_t kBN[kConfigs] = {64, 16, 32, 128, 32, 8, 512, 64, 64};
     const int64_t BM = kBM[g.config], BN = kBN[g.config];
     const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN) * rows;
     g.k_splits = 1;
     g.k_chunk = Kd;
-    if (tiles * 4 <= target && Kd >= 512) {
+    // Chunks of at least 256; of 1024 for a plane kernel's step of every slice: a batch fills the
+    // chip without splits, and each costs a write and a read of the whole output (1.1 of 11.3 ms
+    // of the 30-qubit workload's batch in BF16x3).  The split may not follow the batch: a slice's
+    // bits must not.
+    const int64_t chunk = (g.config >= 7 && !inv) ? 1024 : 256;
+    if (tiles * 4 <= target && Kd >= 2 * chunk) {
       int64_t s = 1;
-      while (tiles * s * 2 <= target && Kd / (s * 2) >= 256) s *= 2;
+      while (tiles * s * 2 <= target && Kd / (s * 2) >= chunk) s *= 2;
       g.k_splits = int(s);
       g.k_chunk = Kd / s;
     }
@@ -747,7 +768,34 @@ struct Compiler {
     g.precision = 0;
     if (plan.precision == TNC_FP16X3) g.precision = 3;
     if (plan.precision == TNC_BF16X3) g.precision = 1;
-    choose_tiles(g, M, N, Kd, rows, !stk.empty());
+    const bool planes =
+        planes_ok(g, !stk.empty(), M, N, int(P.dense.size()), int(Q.dense.size()), finite);
+    if (planes) {
+      std::vector<int32_t> kt;
+      for (int64_t t = 0; t < Kd / 16; ++t) {
+        int32_t oa = 0, ob = 0;
+        for (int j = 4; j < nk; ++j)
+          if ((t >> (j - 4)) & 1) {
+            oa += int32_t(1) << g.a_kpos[j];
+            ob += int32_t(1) << g.b_kpos[j];
+          }
+        kt.push_back(oa);
+        kt.push_back(ob);
+      }
+      L.ktab_off = add_const(kt.data(), kt.size() * sizeof(int32_t));
+      auto spread = [](int64_t x, const int8_t* pos, int n) {
+        int64_t o = 0;
+        for (int j = 0; j < n; ++j) o += ((x >> j) & 1) << pos[j];
+        return o;
+      };
+      std::vector<int64_t> mt, nt;
+      for (int64_t m = 0; m < M; m += 128)
+        mt.push_back((g.fold ? (m >> nm) * g.fold_stride : 0) + spread(m & ((int64_t(1) << nm) - 1), g.a_mpos, nm));
+      for (int64_t n = 0; n < N; n += 64) nt.push_back(spread(n, g.b_npos, nn));
+      L.mtab_off = add_const(mt.data(), mt.size() * sizeof(int64_t));
+      L.ntab_off = add_const(nt.data(), nt.size() * sizeof(int64_t));
+    }
+    choose_tiles(g, M, N, Kd, rows, !stk.empty(), planes, inv);
     if (!stk.empty()) {
       g.k_splits = 1;   // the split-K reduce assumes C in the launch's own layout
       g.k_chunk = Kd;
@@ -772,6 +820,7 @@ struct Compiler {
     L.bufs = {pbuf, qbuf, C.buf};
     int part = -1;
     L.max_splits = g.k_splits;
+    L.planes = g.config >= 7;
     if (g.k_splits > 1) {
       part = new_buf(uint64_t(g.k_splits) * uint64_t(rows) * uint64_t(M) * uint64_t(N) * 8, false,
                      ps);
@@ -1035,6 +1084,9 @@ struct Exec {
         a.gb = gat(L.g1);
         a.stk = gat(L.stk_off);
         a.perm = gat(L.perm_off);
+        a.ktab = gat(L.ktab_off);
+        a.mtab = reinterpret_cast<const int64_t*>(gat(L.mtab_off));
+        a.ntab = reinterpret_cast<const int64_t*>(gat(L.ntab_off));
         a.rec_a = rec(L.rec_in0);
         a.rec_b = rec(L.rec_in1);
         a.rec_c = rec(L.rec_out);
@@ -1447,7 +1499,10 @@ int autotune(tnc_plan_s& p, uint8_t* ws, hipStream_t st, int reps) {
       const std::string key = tune_key(probe, nb);
       std::pair<int, int> best{L.gm.config, L.gm.k_splits};
       auto hit = g_tune.find(key);
-      if (hit != g_tune.end() && hit->second.second <= L.max_splits) {
+      // an entry of a cache file may name a kernel this step cannot run on
+      const bool runs = hit != g_tune.end() && hit->second.first < Compiler::kConfigs &&
+                        (hit->second.first < 7 || L.planes);
+      if (runs && hit->second.second <= L.max_splits) {
         best = hit->second;
       } else {
         // the planned choice is timed first, so that it survives ties
@@ -1458,8 +1513,12 @@ int autotune(tnc_plan_s& p, uint8_t* ws, hipStream_t st, int reps) {
         for (int cfg = 0; cfg < Compiler::kConfigs; ++cfg) {
           if (cfg == 5 && L.gm.precision != 0 && !narrow) continue;
           if (cfg == 6 && !Compiler::outer_ok(L.gm, L.stk_off >= 0)) continue;
-          if (cfg >= 7 && !Compiler::big_ok(L.gm, L.stk_off >= 0)) continue;
-          for (int sp = 1; sp <= (cfg == 6 ? 1 : L.max_splits); sp *= 2)
+          // plane kernels only where they were planned: they round once per plane pair and 16 k,
+          // and a chain of 1024 of the 30-qubit workload's 64 x 64 x 65536 step on them took that
+          // sum's error from 1.1e-6 to 2.6e-5
+          if (cfg >= 7 && !L.planes) continue;
+          const int sp_min = cfg >= 7 ? int(std::min<int64_t>(L.max_splits, std::max<int64_t>(1, L.gm.K / 1024))) : 1;
+          for (int sp = sp_min; sp <= (cfg == 6 ? 1 : L.max_splits); sp *= 2)
             if ((sp == 1 || L.gm.K / sp >= 256) && std::make_pair(cfg, sp) != best)
               cands.push_back({cfg, sp});
         }

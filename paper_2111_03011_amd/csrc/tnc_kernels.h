@@ -88,6 +88,11 @@ struct GemmArgs {
   // offsets within one slice fit in 31 bits.
   const int32_t* stk;
   const int32_t* perm;
+  // k_gemm_planes: element offsets of every 16-k tile in A and B (interleaved), of every 128th
+  // m in A (folded rows included) and of every 64th n in B
+  const int32_t* ktab;
+  const int64_t* mtab;
+  const int64_t* ntab;
   int group_m;                // tiles are numbered in groups of group_m tile rows (L2 reuse)
   // scale records of A, B and C (see kRecWords); with k_splits > 1 the reduction folds
   // C's largest component in, the GEMM writes its exponent
@@ -152,6 +157,7 @@ struct SliceSumArgs {
 // Launchers (return hipError_t of the launch).
 hipError_t launch_stream(const StreamArgs& a, hipStream_t s);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
+hipError_t launch_gemm_planes(const GemmArgs& a, hipStream_t s);
 // whether configuration 5 runs a launch on the narrow-row kernel (k_gemm_rows_narrow),
 // which computes in FP32 in every form
 bool gemm_rows_narrow_fits(const GemmArgs& a, bool stacked);
