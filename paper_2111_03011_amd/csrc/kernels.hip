@@ -1409,10 +1409,14 @@ __global__ void k_add_i64(int64_t* p, int64_t v) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *p += v;
 }
 
-__global__ __launch_bounds__(kThreads) void k_fill_zero(double* p, int64_t n) {
-  for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < n;
-       i += int64_t(gridDim.x) * kThreads)
-    p[i] = 0.0;
+// Start of a contraction, one launch where three took 4 us each: amplitudes and records cleared,
+// slice counter set.
+__global__ __launch_bounds__(kThreads) void k_begin(double* amps, int64_t n_amps, uint32_t* recs, int64_t n_recs,
+                                                    int64_t* counter, int64_t first) {
+  const int64_t i0 = int64_t(blockIdx.x) * kThreads + threadIdx.x, step = int64_t(gridDim.x) * kThreads;
+  for (int64_t i = i0; i < n_amps; i += step) amps[i] = 0.0;
+  for (int64_t i = i0; i < n_recs; i += step) recs[i] = 0u;
+  if (i0 == 0 && counter) *counter = first;
 }
 
 // ---------------------------------------------------------------------------------
@@ -1865,8 +1869,11 @@ hipError_t launch_add_i64(int64_t* p, int64_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_fill_zero(double* p, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, s, p, n);
+hipError_t launch_begin(double* amps, int64_t n_amps, uint32_t* recs, int64_t n_recs, int64_t* counter,
+                        int64_t first, hipStream_t s) {
+  const int64_t n = n_amps > n_recs ? n_amps : n_recs;
+  hipLaunchKernelGGL(k_begin, dim3(grid_for(n > 1 ? n : 1, kThreads)), dim3(kThreads), 0, s, amps, n_amps, recs,
+                     n_recs, counter, first);
   return hipGetLastError();
 }
 

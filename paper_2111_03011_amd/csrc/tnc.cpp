@@ -123,6 +123,7 @@ struct Buf {
   uint64_t off = 0;       // absolute byte offset in the workspace
   int t0 = INT_MAX, t1 = -1;
   bool to_end = false;    // produced once, read by every slice
+  bool in_lds = false;    // lives in a fused program's LDS: no memory of its own
 };
 
 struct Launch {
@@ -144,6 +145,27 @@ struct Launch {
   GemmArgs gm{};
   ReduceArgs rd{};
   tnc_step_info info{};
+  // a small FP32 step, which a fused program may take: its descriptor (offsets and records filled
+  // in at the end), contraction offsets in X and S, operands (X, S, C)
+  bool small = false, fused = false;
+  ProgStep ps{};
+  std::vector<int32_t> kx, ks;
+  int p_buf[3] = {-1, -1, -1}, p_rec[3] = {-1, -1, -1};
+};
+
+// What one launch of the device executes: a step, or a fused program of small steps (trees of a
+// forest, in step order).  The lists of launches stay in path order.
+struct Unit {
+  std::vector<int> steps;     // indices in the launch list
+  bool program = false;
+  int cls = 0;                // 0: once per call, 1: once per batch, 2: per slice
+  std::vector<std::vector<int>> trees;
+  std::vector<std::vector<std::pair<int, int>>> rounds;   // of each tree: first step, steps (ProgTree)
+  std::vector<ProgTree> layout;                 // of each tree, with the places of its tables
+  std::vector<std::map<int, int>> slot, place;  // of each tree: record -> LDS, staged operand -> LDS
+  std::vector<int> leaf_at;                     // of each tree: first constant operand in LDS
+  int lds_elems = 0, n_ext = 0;
+  int64_t trees_off = 0, ext_off = 0;           // constants block
 };
 
 struct TState {
@@ -166,6 +188,8 @@ struct TimingRec {
   int index;   // launch index (invariant launches first), -1 if not one of the plan's
   double bytes, flops;
   hipEvent_t e0, e1;
+  int64_t nb;
+  std::vector<int> fused;   // a program's launch indices: its time is shared out evenly
 };
 
 }  // namespace
@@ -188,6 +212,8 @@ struct tnc_plan_s {
   std::vector<uint8_t> consts;
   uint64_t consts_bytes = 0, ws_bytes = 0;
   std::vector<Launch> inv, dep;
+  std::vector<Unit> units[2];        // of inv and dep
+  std::vector<uint32_t> const_amax;  // largest component of each constant record
 
   // slice leaves
   std::vector<SliceLeafEntry> sl_table;
@@ -374,7 +400,7 @@ struct Compiler {
       uint32_t bits;
       std::memcpy(&bits, &mx, 4);
       s.rec = new_rec(REC_CONST, false);
-      const_amax.push_back(bits);
+      plan.const_amax.push_back(bits);
       if (sl.empty()) {
         s.buf = const_buf(host.data(), host.size() * sizeof(float));
       } else {
@@ -559,13 +585,12 @@ struct Compiler {
     plan.recs.push_back(r);
     return int(plan.recs.size() - 1);
   }
-  std::vector<uint32_t> const_amax;   // largest component of each constant record
 
   // the record blocks and their clearing launches, once every tensor has its record
   void finish_records() {
     std::vector<uint32_t> words(size_t(plan.rec_count[REC_CONST]) * kRecWords, 0u);
-    for (size_t i = 0; i < const_amax.size(); ++i)
-      for (int j = 0; j < kAmaxSlots; ++j) words[i * kRecWords + j] = const_amax[i];
+    for (size_t i = 0; i < plan.const_amax.size(); ++i)
+      for (int j = 0; j < kAmaxSlots; ++j) words[i * kRecWords + j] = plan.const_amax[i];
     if (!words.empty()) plan.rec_buf[REC_CONST] = const_buf(words.data(), words.size() * 4);
     for (int blk : {REC_INV, REC_DEP}) {
       if (plan.rec_count[blk] == 0) continue;
@@ -583,6 +608,295 @@ struct Compiler {
       std::vector<Launch>& lst = list(Z.inv);
       lst.insert(lst.begin(), Z);
     }
+  }
+
+  // Whether a step is small enough for a fused program (program.hip), and its descriptor.  X
+  // supplies m, S supplies n; C is [row][m][n].  Up to 2^16 multiply-adds and 2^14 outputs: the
+  // smallest steps take a wave 1.2 us, the largest a workgroup 4 to 9 us, and a launch of its own
+  // 4.5 us and more in a chain of launches.  Measured, programs off and on: 3 x 4, 8 cycles, 64
+  // amplitudes (27 steps) 139 -> 44 us, all 4096 in FP16x3 152 -> 69 us; 4 x 5, 11 cycles, 16 slices
+  // by 5000 groups 0.67 -> 0.27 ms; 4 x 6, 12 cycles, 64 slices 2.5 -> 2.0 ms; the 53-qubit share in
+  // subtasks of 8 slices 67 -> 51 ms.  A split form's plan fuses its streams alone, whose bits stay
+  // what they were: its GEMM steps keep their arithmetic.
+  void small_step(Launch& L, const TState& X, const TState& S, const TState& C, const std::vector<int32_t>& MX,
+                  const std::vector<int32_t>& NS, const std::vector<int32_t>& K) {
+    const int nm = int(MX.size()), nn = int(NS.size()), nk = int(K.size());
+    if (nk > 8 || nm > 14 || nn > 14 || C.rows() > 16384) return;
+    if ((C.rows() << (nm + nn)) > 16384 || (C.rows() << (nm + nn + nk)) > 65536) return;
+    if (X.elems() > (1 << 24) || S.elems() > (1 << 24)) return;
+    ProgStep& p = L.ps;
+    auto runs = [&](const TState& T, const std::vector<int32_t>& lab, ProgBits* out, uint8_t& n) {
+      n = 0;
+      const int k = int(lab.size());
+      for (int j = 0; j < k;) {
+        const int pos = pos_of(T.dense, lab[size_t(k - 1 - j)]);
+        int len = 1;
+        while (j + len < k && pos_of(T.dense, lab[size_t(k - 1 - j - len)]) == pos + len) ++len;
+        if (n == kProgBits) return false;
+        out[n++] = ProgBits{uint8_t(j), uint8_t(len), uint8_t(pos), 0};
+        j += len;
+      }
+      return true;
+    };
+    if (!runs(X, MX, p.mr, p.n_mr) || !runs(S, NS, p.nr, p.n_nr)) return;
+    p.rows = int32_t(C.rows());
+    p.nm = uint8_t(nm);
+    p.nn = uint8_t(nn);
+    p.nk = uint8_t(nk);
+    p.x_row = uint8_t(X.dense.size());
+    p.s_row = uint8_t(S.dense.size());
+    p.x_one = X.rows() == 1;
+    p.s_one = S.rows() == 1;
+    p.x_elems = int32_t(X.elems());
+    p.s_elems = int32_t(S.elems());
+    p.flags = (nn >= 2 && (C.rows() << (nm + nn)) >= 2048) ? 8 : 0;
+    for (int64_t k = 0; k < (int64_t(1) << nk); ++k) {
+      int32_t ox = 0, os = 0;
+      for (int j = 0; j < nk; ++j)
+        if ((k >> j) & 1) {
+          ox += int32_t(1) << pos_of(X.dense, K[size_t(nk - 1 - j)]);
+          os += int32_t(1) << pos_of(S.dense, K[size_t(nk - 1 - j)]);
+        }
+      L.kx.push_back(ox);
+      L.ks.push_back(os);
+    }
+    L.p_buf[0] = X.buf, L.p_buf[1] = S.buf, L.p_buf[2] = C.buf;
+    L.p_rec[0] = X.rec, L.p_rec[1] = S.rec, L.p_rec[2] = C.rec;
+    p.x_slice = sstride(X.buf);
+    p.s_slice = sstride(S.buf);
+    p.c_slice = sstride(C.buf);
+    p.gx = L.g0;
+    p.gs = L.g1;
+    L.small = true;
+  }
+
+  // The units of a launch list.  A small step joins the earliest program of its class (once per
+  // call, once per batch, per slice) that its operands allow: none may be produced in a later
+  // unit.  A tree's size is bounded by the kernel's tables and by its work, so that no workgroup
+  // is the last by far.
+  void make_units(std::vector<Launch>& lst, std::vector<Unit>& units, bool fuse) {
+    std::map<int, int> made_in, made_by;      // buffer -> unit, launch
+    std::vector<int> tree_of(lst.size(), -1);
+    for (int i = 0; i < int(lst.size()); ++i) {
+      Launch& L = lst[size_t(i)];
+      int at = -1;
+      if (fuse && L.small) {
+        const int cls = L.inv ? 0 : (L.shared ? 1 : 2);
+        int need = 0;
+        for (int x = 0; x < 2; ++x)
+          if (made_in.count(L.p_buf[x])) need = std::max(need, made_in[L.p_buf[x]]);
+        for (int u = need; u < int(units.size()) && at < 0; ++u) {
+          Unit& U = units[size_t(u)];
+          if (!U.program || U.cls != cls) continue;
+          // the trees it would join
+          std::vector<int> joined{i};
+          int keep = -1, gone = -1;
+          for (int x = 0; x < 2; ++x) {
+            auto it = made_by.find(L.p_buf[x]);
+            if (it == made_by.end() || made_in[L.p_buf[x]] != u) continue;
+            const int t = tree_of[size_t(it->second)];
+            if (keep < 0) keep = t;
+            else if (t != keep) gone = t;
+          }
+          for (int t : {keep, gone})
+            if (t >= 0) joined.insert(joined.end(), U.trees[size_t(t)].begin(), U.trees[size_t(t)].end());
+          size_t k = 0;
+          int64_t macs = 0;
+          for (int j : joined) {
+            const ProgStep& p = lst[size_t(j)].ps;
+            k += lst[size_t(j)].kx.size();
+            macs += int64_t(p.rows) << (p.nm + p.nn + p.nk);
+          }
+          if (int(joined.size()) > kProgMaxSteps || k > size_t(kProgMaxK) || macs > (int64_t(1) << 19) ||
+              joined.size() * (sizeof(ProgStep) / 8 + 4) + k + 8 > size_t(kProgTables))
+            continue;
+          std::sort(joined.begin(), joined.end());
+          if (keep < 0) {
+            keep = int(U.trees.size());
+            U.trees.emplace_back();
+          }
+          U.trees[size_t(keep)] = joined;
+          if (gone >= 0) U.trees[size_t(gone)].clear();
+          for (int j : joined) tree_of[size_t(j)] = keep;
+          U.steps.push_back(i);
+          at = u;
+        }
+        if (at < 0) {
+          Unit U;
+          U.program = true;
+          U.cls = cls;
+          U.steps = {i};
+          U.trees = {{i}};
+          tree_of[size_t(i)] = 0;
+          units.push_back(U);
+          at = int(units.size()) - 1;
+        }
+        L.fused = true;
+        made_by[L.p_buf[2]] = i;
+        made_in[L.p_buf[2]] = at;
+        continue;
+      }
+      Unit U;
+      U.steps = {i};
+      units.push_back(U);
+      at = int(units.size()) - 1;
+      if (L.kind == K_LEAVES)
+        for (int b : L.bufs) made_in[b] = at;
+      else if (L.b_out >= 0)
+        made_in[L.b_out] = at;
+    }
+    for (Unit& U : units)
+      if (U.program) place_program(lst, U);
+  }
+
+  // A program's LDS: per tree its tables, the operands from outside that fit (constants come with
+  // the tables as one image, the others are copied from their buffers), then the intermediates
+  // (first fit, by lifetime; one that does not fit keeps its buffer).
+  void place_program(std::vector<Launch>& lst, Unit& U) {
+    std::vector<std::vector<int>> trees;
+    for (auto& t : U.trees)
+      if (!t.empty()) trees.push_back(t);
+    U.trees = trees;
+    std::sort(U.steps.begin(), U.steps.end());
+    for (auto& tree : U.trees) {
+      // Rounds: the steps of one depth in the tree are independent.  Those of at most 256 outputs
+      // and 2^12 multiply-adds go to one wave each, as many at a time as there are waves; a larger
+      // one takes the workgroup.  (Such a step costs its latencies, about 1.2 us: 20 of them one
+      // after the other were half the time of a 3 x 4, 8-cycle circuit.)
+      std::map<int, int> depth_of;                  // buffer -> depth
+      std::map<int, std::vector<int>> by_depth;
+      for (int j : tree) {
+        const Launch& L = lst[size_t(j)];
+        int d = 0;
+        for (int o = 0; o < 2; ++o)
+          if (depth_of.count(L.p_buf[o])) d = std::max(d, depth_of[L.p_buf[o]] + 1);
+        depth_of[L.p_buf[2]] = d;
+        by_depth[d].push_back(j);
+      }
+      std::vector<std::pair<int, int>> rounds;
+      tree.clear();
+      for (auto& kv : by_depth) {
+        std::vector<int> wide;
+        int n = 0;
+        for (int j : kv.second) {
+          const ProgStep& p = lst[size_t(j)].ps;
+          const int64_t out = int64_t(p.rows) << (p.nm + p.nn);
+          if (out > 256 || (out << p.nk) > 4096) {
+            wide.push_back(j);
+            continue;
+          }
+          if (n % (kProgThreads / 64) == 0) rounds.push_back({int(tree.size()), 0});
+          ++rounds.back().second;
+          tree.push_back(j);
+          ++n;
+        }
+        for (int j : wide) {
+          rounds.push_back({int(tree.size()), 0});
+          tree.push_back(j);
+        }
+      }
+      U.rounds.push_back(rounds);
+      std::set<int> made;
+      for (int j : tree) made.insert(lst[size_t(j)].p_buf[2]);
+      struct Op {
+        int buf, rec, elems;
+      };
+      std::vector<Op> ops;            // from outside the tree
+      size_t n_k = 0;
+      for (int j : tree) {
+        const Launch& L = lst[size_t(j)];
+        n_k += L.kx.size();
+        for (int o = 0; o < 2; ++o)
+          if (!made.count(L.p_buf[o]))
+            ops.push_back(Op{L.p_buf[o], L.p_rec[o], o ? L.ps.s_elems : L.ps.x_elems});
+      }
+      ProgTree T{};
+      std::map<int, int> slot, place;
+      int at = 0;
+      for (auto& o : ops)
+        if (plan.recs[size_t(o.rec)].block != REC_CONST) slot[o.rec] = at++;
+      at = T.img_at = (at + 1) & ~1;
+      for (auto& o : ops)
+        if (plan.recs[size_t(o.rec)].block == REC_CONST) slot[o.rec] = at++;
+      for (int j : tree) slot[lst[size_t(j)].p_rec[2]] = at++;
+      for (int j : tree) {
+        lst[size_t(j)].ps.k0 = at;
+        at += int(lst[size_t(j)].kx.size());
+      }
+      T.round0 = at;
+      T.n_rounds = int32_t(rounds.size());
+      at += T.n_rounds;
+      T.step0 = at;
+      T.n_steps = int32_t(tree.size());
+      at += T.n_steps * int(sizeof(ProgStep) / 8);
+      const int leaf_at = at;
+      // the smaller operands first; constants end the image
+      std::stable_sort(ops.begin(), ops.end(), [](const Op& a, const Op& b) { return a.elems < b.elems; });
+      std::map<int, std::pair<int, int>> live;      // buffer -> LDS place and size
+      auto room = [](int n) { return n > 32 ? (n + 31) & ~31 : n; };
+      int total = at;
+      for (int pass = 0; pass < 2; ++pass) {
+        for (auto& o : ops) {
+          if (plan.bufs[size_t(o.buf)].is_const != (pass == 0) || total + room(o.elems) > kProgStage) continue;
+          live[o.buf] = {at, room(o.elems)};
+          place[o.buf] = at;
+          at += room(o.elems);
+          total = at;
+        }
+        if (pass == 0) {
+          at += at & 1;
+          T.img_n = (at - T.img_at) / 2;
+        }
+      }
+      U.lds_elems = std::max(U.lds_elems, at);
+      for (auto& rd : rounds) {                     // operands stay to the end of the round
+        const size_t x0 = size_t(rd.first), x1 = x0 + size_t(std::max(1, rd.second));
+        for (size_t x = x0; x < x1; ++x) {
+          Launch& L = lst[size_t(tree[x])];
+          ProgStep& p = L.ps;
+          for (int o = 0; o < 2; ++o)
+            if (live.count(L.p_buf[o])) {
+              p.flags |= 1 << o;
+              (o ? p.s : p.x) = live[L.p_buf[o]].first;
+            }
+          if (x + 1 == tree.size()) break;
+          const int size = room(p.rows << (p.nm + p.nn));
+          std::vector<std::pair<int, int>> busy;
+          for (auto& kv : live) busy.push_back(kv.second);
+          std::sort(busy.begin(), busy.end());
+          int c = leaf_at;
+          for (auto& b : busy) {
+            if (c + size <= b.first) break;
+            c = std::max(c, b.first + b.second);
+          }
+          if (c + size > kProgLds) continue;
+          p.flags |= 4;
+          p.c = c;
+          live[L.p_buf[2]] = {c, size};
+          plan.bufs[size_t(L.p_buf[2])].in_lds = true;
+          U.lds_elems = std::max(U.lds_elems, c + size);
+        }
+        for (size_t x = x0; x < x1; ++x)
+          for (int o = 0; o < 2; ++o) live.erase(lst[size_t(tree[x])].p_buf[o]);
+      }
+      T.ext0 = U.n_ext;
+      for (auto& o : ops)
+        T.n_ext += plan.recs[size_t(o.rec)].block != REC_CONST ||
+                   (!plan.bufs[size_t(o.buf)].is_const && place.count(o.buf));
+      U.n_ext += T.n_ext;
+      const std::vector<uint8_t> zero(size_t(T.img_n) * 16, 0);
+      T.image = add_const(zero.data(), zero.size());
+      U.layout.push_back(T);
+      U.slot.push_back(slot);
+      U.place.push_back(place);
+      U.leaf_at.push_back(leaf_at);
+    }
+    auto room = [&](size_t bytes) {
+      const std::vector<uint8_t> zero(bytes, 0);
+      return add_const(zero.data(), bytes);
+    };
+    U.trees_off = room(U.trees.size() * sizeof(ProgTree));
+    U.ext_off = room(size_t(U.n_ext) * sizeof(ProgExt));
   }
 
   TState step(TState& A, TState& B) {
@@ -663,6 +977,8 @@ struct Compiler {
       L.info = tnc_step_info{K_STREAM, inv, C.rows(), int64_t(1) << a.n_m, int64_t(1) << a.nn,
                              int64_t(1) << nk, 8.0 * macs,
                              8.0 * double(X.elems() + S.elems() + C.elems())};
+      // the stream kernels' order of k, so that the step's bits are theirs
+      small_step(L, X, S, C, MX, NS, std::vector<int32_t>(K.rbegin(), K.rend()));
       account(L);
       list(inv).push_back(L);
       return C;
@@ -829,6 +1145,7 @@ struct Compiler {
     }
     L.info = tnc_step_info{K_GEMM, inv, rows_c, m_c, N, Kd, 8.0 * macs,
                            8.0 * double(P.elems() + Q.elems() + C.elems())};
+    if (part < 0 && plan.precision == TNC_C64) small_step(L, P, Q, C, MP, NQ, KP);
     account(L);
     list(inv).push_back(L);
     if (part >= 0) {
@@ -913,24 +1230,30 @@ struct Compiler {
     plan.b_samples = new_buf(uint64_t(plan.sample_chunk) * 8);
     plan.b_counter = new_buf(8);
     finish_records();
+    // a plan of a few steps keeps their own kernels; TNC_NO_FUSE=1 turns programs off
+    int n_small = 0;
+    for (auto* l : {&plan.inv, &plan.dep})
+      for (auto& x : *l) n_small += x.small;
+    const bool fuse = n_small >= 4 && std::getenv("TNC_NO_FUSE") == nullptr;
+    make_units(plan.inv, plan.units[0], fuse);
+    make_units(plan.dep, plan.units[1], fuse);
   }
 };
 
 void pack(tnc_plan_s& plan) {
-  // lifetimes: phase-1 launches occupy [0, P), phase-2 launches [P, P + D)
-  const int P = int(plan.inv.size()), D = int(plan.dep.size());
+  // lifetimes: phase-1 units occupy [0, P), phase-2 units [P, P + D)
+  const int P = int(plan.units[0].size()), D = int(plan.units[1].size());
   const int END = P + D;
   auto touch = [&](int b, int t) {
     Buf& x = plan.bufs[b];
     x.t0 = std::min(x.t0, t);
     x.t1 = std::max(x.t1, t);
   };
-  for (int i = 0; i < P; ++i)
-    for (int b : plan.inv[i].bufs) touch(b, i);
-  for (int i = 0; i < D; ++i)
-    for (int b : plan.dep[i].bufs) touch(b, P + i);
+  for (int i = 0; i < P + D; ++i)
+    for (int l : i < P ? plan.units[0][size_t(i)].steps : plan.units[1][size_t(i - P)].steps)
+      for (int b : (i < P ? plan.inv : plan.dep)[size_t(l)].bufs) touch(b, i);
   for (auto& b : plan.bufs) {
-    if (b.is_const) continue;
+    if (b.is_const || b.in_lds) continue;
     if (b.t1 < 0) { b.t0 = 0; b.t1 = END; }          // scratch kept for the whole call
     if (b.t0 < P && b.t1 >= P) b.to_end = true;       // invariant result read by slices
     if (b.to_end) b.t1 = END;
@@ -938,7 +1261,7 @@ void pack(tnc_plan_s& plan) {
   plan.consts_bytes = align_up(plan.consts.size());
   std::vector<int> order;
   for (size_t i = 0; i < plan.bufs.size(); ++i)
-    if (!plan.bufs[i].is_const) order.push_back(int(i));
+    if (!plan.bufs[i].is_const && !plan.bufs[i].in_lds) order.push_back(int(i));
   std::sort(order.begin(), order.end(), [&](int a, int b) {
     return plan.bufs[a].bytes != plan.bufs[b].bytes ? plan.bufs[a].bytes > plan.bufs[b].bytes : a < b;
   });
@@ -969,6 +1292,80 @@ void pack(tnc_plan_s& plan) {
   if (!plan.sl_table.empty())
     std::memcpy(plan.consts.data() + plan.sl_table_off, plan.sl_table.data(),
                 plan.sl_table.size() * sizeof(SliceLeafEntry));
+  // the programs' tables hold workspace offsets
+  auto rec_words = [&](int r) {
+    const Rec& x = plan.recs[size_t(r)];
+    return int64_t(plan.bufs[size_t(plan.rec_buf[x.block])].off / 4) + x.index * kRecWords;
+  };
+  auto rec_step = [&](int r) {
+    const Rec& x = plan.recs[size_t(r)];
+    return x.per_slice ? plan.rec_count[x.block] * kRecWords : 0;
+  };
+  for (int ph = 0; ph < 2; ++ph) {
+    std::vector<Launch>& lst = ph == 0 ? plan.inv : plan.dep;
+    for (Unit& U : plan.units[ph]) {
+      if (!U.program) continue;
+      std::vector<ProgExt> ext;
+      for (size_t t = 0; t < U.trees.size(); ++t) {
+        ProgTree& T = U.layout[t];
+        std::vector<int64_t> image(size_t(T.img_n) * 2, 0);
+        auto unit = [&](int at) { return &image[size_t(at - T.img_at)]; };
+        for (size_t i = 0; i < U.rounds[t].size(); ++i) {
+          const int32_t v[2] = {U.rounds[t][i].first, U.rounds[t][i].second};
+          std::memcpy(unit(T.round0 + int(i)), v, 8);
+        }
+        std::set<int> made;
+        for (int j : U.trees[t]) made.insert(lst[size_t(j)].p_buf[2]);
+        for (size_t x = 0; x < U.trees[t].size(); ++x) {
+          Launch& L = lst[size_t(U.trees[t][x])];
+          for (int o = 0; o < 2; ++o) {
+            const int b = L.p_buf[o], r = L.p_rec[o], n = o ? L.ps.s_elems : L.ps.x_elems;
+            if (made.count(b)) continue;
+            const bool rec_const = plan.recs[size_t(r)].block == REC_CONST;
+            const bool staged = U.place[t].count(b) > 0, c = plan.bufs[size_t(b)].is_const;
+            if (rec_const) {
+              const int32_t v[2] = {int32_t(plan.const_amax[size_t(plan.recs[size_t(r)].index)]), 0};
+              std::memcpy(unit(U.slot[t][r]), v, 8);
+            }
+            if (staged && c)
+              for (int i = 0; i < n; ++i)
+                std::memcpy(unit(U.place[t][b] + prog_swz(i)), plan.consts.data() + plan.bufs[size_t(b)].off + 8 * size_t(i), 8);
+            if (rec_const && (c || !staged)) continue;
+            ProgExt e{};
+            e.rec = rec_const ? -1 : rec_words(r);
+            e.rec_step = rec_step(r);
+            e.slot = U.slot[t][r];
+            if (staged && !c) {
+              e.src = int64_t(plan.bufs[size_t(b)].off / 8);
+              e.src_slice = o ? L.ps.s_slice : L.ps.x_slice;
+              e.dst = U.place[t][b];
+              e.count = n;
+            }
+            ext.push_back(e);
+          }
+          ProgStep p = L.ps;
+          if (!(p.flags & 1)) p.x = int64_t(plan.bufs[size_t(L.p_buf[0])].off / 8);
+          if (!(p.flags & 2)) p.s = int64_t(plan.bufs[size_t(L.p_buf[1])].off / 8);
+          if (!(p.flags & 4)) p.c = int64_t(plan.bufs[size_t(L.p_buf[2])].off / 8);
+          p.rec_x = U.slot[t][L.p_rec[0]];
+          p.rec_s = U.slot[t][L.p_rec[1]];
+          p.rec_c = U.slot[t][L.p_rec[2]];
+          std::memcpy(unit(T.step0 + int(x * sizeof(ProgStep) / 8)), &p, sizeof(p));
+          for (size_t k = 0; k < L.kx.size(); ++k) {
+            const int32_t v[2] = {(p.flags & 1) ? prog_swz(L.kx[k]) : L.kx[k],
+                                  (p.flags & 2) ? prog_swz(L.ks[k]) : L.ks[k]};
+            std::memcpy(unit(p.k0 + int(k)), v, 8);
+          }
+        }
+        const int root = lst[size_t(U.trees[t].back())].p_rec[2];
+        T.rec_out = rec_words(root);
+        T.rec_out_step = rec_step(root);
+        std::memcpy(plan.consts.data() + T.image, image.data(), image.size() * 8);
+      }
+      std::memcpy(plan.consts.data() + U.trees_off, U.layout.data(), U.layout.size() * sizeof(ProgTree));
+      std::memcpy(plan.consts.data() + U.ext_off, ext.data(), ext.size() * sizeof(ProgExt));
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------
@@ -1148,14 +1545,40 @@ struct Exec {
       else if (!p.dep.empty() && &L >= p.dep.data() && &L < p.dep.data() + p.dep.size())
         index = int(p.inv.size()) + int(&L - p.dep.data());
       p.pending.push_back(
-          TimingRec{L.kind, index, L.info.bytes * double(nb), L.info.flops * double(nb), e0, e1});
+          TimingRec{L.kind, index, L.info.bytes * double(nb), L.info.flops * double(nb), e0, e1, nb, {}});
     }
   }
 
-  // the per-batch program: every slice-dependent launch, then the slice counter advance
-  void batch(int64_t nb, double* amps, hipStream_t st, bool timed) {
-    for (auto& L : p.dep) launch(L, nb, amps, st, timed);
-    check(launch_add_i64(counter(), nb, st));
+  // one unit of a phase for nb slices
+  void unit(int ph, const Unit& U, int64_t nb, double* amps, hipStream_t st, bool timed) {
+    const std::vector<Launch>& lst = ph == 0 ? p.inv : p.dep;
+    if (!U.program) return launch(lst[size_t(U.steps[0])], nb, amps, st, timed);
+    ProgArgs a{};
+    a.ws = ws;
+    a.trees = reinterpret_cast<const ProgTree*>(ws + U.trees_off);
+    a.ext = reinterpret_cast<const ProgExt*>(ws + U.ext_off);
+    a.nb = U.cls == 2 ? nb : 1;
+    a.n_trees = int(U.trees.size());
+    a.lds_elems = U.lds_elems;
+    TimingRec r{};
+    if (timed) {
+      r.e0 = ev();
+      r.e1 = ev();
+      HIPCHK(hipEventRecord(r.e0, st));
+    }
+    check(launch_program(a, st));
+    if (timed) {
+      HIPCHK(hipEventRecord(r.e1, st));
+      r.nb = nb;
+      for (int j : U.steps) r.fused.push_back(j + (ph == 0 ? 0 : int(p.inv.size())));
+      p.pending.push_back(r);
+    }
+  }
+
+  // the per-batch program: every slice-dependent unit, then the slice counter advance
+  void batch(int64_t nb, double* amps, hipStream_t st, bool timed, bool last = false) {
+    for (auto& U : p.units[1]) unit(1, U, nb, amps, st, timed);
+    if (!last) check(launch_add_i64(counter(), nb, st));
   }
 
   void capture(double* amps) {
@@ -1195,13 +1618,28 @@ struct Exec {
                 bool skip_invariant = false) {
     upload();
     const int64_t n_amp = p.L << p.n_open;
-    if (!accumulate) check(launch_fill_zero(amps, 2 * n_amp, s));
-    if (count <= 0) return;
+    const int64_t n_clear = accumulate ? 0 : 2 * n_amp;
+    if (count <= 0) {
+      if (n_clear) check(launch_begin(amps, n_clear, nullptr, 0, nullptr, 0, s));
+      return;
+    }
+    // one launch clears the amplitudes and the records of the invariant steps, and sets the counter
+    size_t u0 = 0;
+    uint32_t* recs = nullptr;
+    int64_t n_recs = 0;
+    if (!skip_invariant && !p.timing && !p.units[0].empty() && !p.units[0][0].program) {
+      const Launch& L = p.inv[size_t(p.units[0][0].steps[0])];
+      if (L.kind == K_SPLIT) {
+        recs = reinterpret_cast<uint32_t*>(ptr(L.b_out));
+        n_recs = L.n_elems;
+        u0 = 1;
+      }
+    }
+    check(launch_begin(amps, n_clear, recs, n_recs, counter(), first, s));
     if (!skip_invariant) {
       tick();
-      for (auto& L : p.inv) launch(L, 1, amps, s, p.timing);
+      for (size_t u = u0; u < p.units[0].size(); ++u) unit(0, p.units[0][u], 1, amps, s, p.timing);
     }
-    check(launch_set_i64(counter(), first, s));
     const int64_t S = p.batch;
     static const bool no_graph = std::getenv("TNC_NO_GRAPH") != nullptr;
     // Full batches replay the captured graph.  With timing on, a bounded sample of batches
@@ -1218,8 +1656,8 @@ struct Exec {
       const int64_t nb = run_length(p, first + pos, count - pos);
       const bool timed = p.timing && (b % stride == 0);
       tick();
-      if (timed || no_graph || nb < S) {
-        batch(nb, amps, s, timed);
+      if (timed || no_graph || nb < S || p.units[1].size() <= 3) {   // a graph of 3 launches costs more than they do
+        batch(nb, amps, s, timed, pos + nb >= count);
       } else {
         if (!captured) capture(amps);
         captured = true;
@@ -1235,19 +1673,26 @@ void harvest(tnc_plan_s& p) {
     HIPCHK(hipEventSynchronize(r.e1));
     float ms = 0;
     HIPCHK(hipEventElapsedTime(&ms, r.e0, r.e1));
-    p.t_ms[r.kind] += ms;
-    p.t_bytes[r.kind] += r.bytes;
-    p.t_flops[r.kind] += r.flops;
-    p.t_n[r.kind] += 1;
-    if (r.index >= 0) {
-      const size_t n = p.inv.size() + p.dep.size();
-      if (p.l_ms.size() != n) {
-        p.l_ms.assign(n, 0.0);
-        p.l_n.assign(n, 0);
-      }
-      p.l_ms[size_t(r.index)] += ms;
-      p.l_n[size_t(r.index)] += 1;
+    const size_t n = p.inv.size() + p.dep.size();
+    if (p.l_ms.size() != n) {
+      p.l_ms.assign(n, 0.0);
+      p.l_n.assign(n, 0);
     }
+    auto add = [&](int kind, int index, double t, double bytes, double flops) {
+      p.t_ms[kind] += t;
+      p.t_bytes[kind] += bytes;
+      p.t_flops[kind] += flops;
+      p.t_n[kind] += 1;
+      if (index < 0) return;
+      p.l_ms[size_t(index)] += t;
+      p.l_n[size_t(index)] += 1;
+    };
+    for (int j : r.fused) {
+      const Launch& L = size_t(j) < p.inv.size() ? p.inv[size_t(j)] : p.dep[size_t(j) - p.inv.size()];
+      const double copies = (L.inv || L.shared) ? 1.0 : double(r.nb);
+      add(L.kind, j, ms / double(r.fused.size()), L.info.bytes * copies, L.info.flops * copies);
+    }
+    if (r.fused.empty()) add(r.kind, r.index, ms, r.bytes, r.flops);
   }
   p.pending.clear();
   p.ev_used = 0;
@@ -1488,7 +1933,7 @@ int autotune(tnc_plan_s& p, uint8_t* ws, hipStream_t st, int reps) {
     std::vector<Launch>& lst = phase == 0 ? p.inv : p.dep;
     for (size_t i = 0; i < lst.size(); ++i) {
       Launch& L = lst[i];
-      if (L.kind != K_GEMM) continue;
+      if (L.kind != K_GEMM || L.fused) continue;
       const int64_t nb = (phase == 0 || L.shared) ? 1 : p.batch;
       Launch* R = (i + 1 < lst.size() && lst[i + 1].kind == K_REDUCE && lst[i + 1].b_in0 == L.b_tmp)
                       ? &lst[i + 1] : nullptr;

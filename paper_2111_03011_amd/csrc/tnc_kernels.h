@@ -102,6 +102,63 @@ struct GemmArgs {
   int64_t rec_a_step, rec_b_step, rec_c_step;
 };
 
+// Fused programs of small steps (program.hip).  A step is C[r][m][n] = sum_k X[gx(r)][m (+) k]
+// S[gs(r)][k, n]; offsets are in complex64 elements, from the workspace's start or in LDS.
+constexpr int kProgThreads = 1024;
+constexpr int kProgLds = 8192;        // LDS of a tree in 8-byte units: tables, operands, intermediates
+constexpr int kProgTables = 3072;     // of them at most for the tables
+constexpr int kProgStage = 5632;      // tables and operands from outside
+constexpr int kProgMaxSteps = 64;     // of one tree
+constexpr int kProgMaxK = 1024;       // entries of its contraction tables
+constexpr int kProgBits = 6;          // runs of consecutive index bits
+
+struct ProgBits {                     // bits [src, src + len) of an index go to [dst, dst + len)
+  uint8_t src, len, dst, pad;
+};
+
+// Element i of a tensor in LDS stands at prog_swz(i): strides of 2^j elements, which a
+// contraction's operands have, then meet no bank twice.  Linear over exclusive or; moves elements
+// inside aligned groups of 32 only.
+__host__ __device__ constexpr int prog_swz(int i) { return i ^ ((i >> 5) & 31); }
+
+struct ProgStep {                     // its 40 words are read one per lane
+  int64_t x, s, c;                    // elements of the workspace, or 8-byte units of LDS
+  int64_t x_slice, s_slice, c_slice;  // per slice copy (0: shared)
+  int64_t gx, gs;                     // bytes from the workspace's start; -1: no gather
+  int32_t rows, k0;                   // k0: first entry of the contraction table (8-byte units of LDS)
+  int32_t rec_x, rec_s, rec_c;        // records (8-byte units of LDS: largest component, exponent)
+  int32_t flags;                      // 1, 2, 4: X, S, C in LDS; 8: four n per thread
+  int32_t x_elems, s_elems;
+  uint8_t nm, nk, nn, x_row;          // log2 of M, K, N and of the row strides
+  uint8_t s_row, x_one, s_one, n_mr;  // x_one: a single row (no gather); n_mr, n_nr: runs in use
+  uint8_t n_nr, pad[3];
+  ProgBits mr[kProgBits], nr[kProgBits];
+  int32_t pad2;
+};
+static_assert(sizeof(ProgStep) == 160, "k_program reads its words by number");
+
+struct ProgExt {                      // a tensor that the tree takes from another launch
+  int64_t rec, rec_step;              // its record in words of the workspace (-1: constant), per slice
+  int64_t src, src_slice;             // its elements, where they are copied to LDS
+  int32_t slot, dst, count, pad;      // record's place; elements' place and number (0: not copied)
+};
+
+struct ProgTree {
+  int64_t image;                      // bytes from the workspace's start: tables and constant operands,
+  int32_t img_at, img_n;              // which stand in LDS from img_at on, img_n 16-byte units
+  int32_t ext0, n_ext, step0, n_steps;   // step0, round0: 8-byte units of LDS
+  int32_t round0, n_rounds;           // a round: first step and number of steps (0: one by the workgroup)
+  int64_t rec_out, rec_out_step;      // the result's record, in words
+};
+
+struct ProgArgs {
+  uint8_t* ws;
+  const ProgTree* trees;
+  const ProgExt* ext;
+  int64_t nb;
+  int n_trees, lds_elems;
+};
+
 struct ReduceArgs {           // C[i] = sum_s partial[s][i]  (i over every slice of the launch)
   const float2* partial;
   float2* C;
@@ -163,10 +220,12 @@ hipError_t launch_gemm_planes(const GemmArgs& a, hipStream_t s);
 bool gemm_rows_narrow_fits(const GemmArgs& a, bool stacked);
 // p[0..n) = 0 (clears scale records before their producers fold into them)
 hipError_t launch_zero_u32(uint32_t* p, int64_t n, hipStream_t s);
+hipError_t launch_program(const ProgArgs& a, hipStream_t s);
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s);
 hipError_t launch_slice_leaves(const SliceLeafArgs& a, int64_t total_elems, hipStream_t s);
 hipError_t launch_slice_sum(const SliceSumArgs& a, hipStream_t s);
-hipError_t launch_fill_zero(double* p, int64_t n_doubles, hipStream_t s);
+hipError_t launch_begin(double* amps, int64_t n_amps, uint32_t* recs, int64_t n_recs, int64_t* counter,
+                        int64_t first, hipStream_t s);
 // *p = v; *p += v (single-thread kernels: safe inside captured graphs)
 hipError_t launch_set_i64(int64_t* p, int64_t v, hipStream_t s);
 hipError_t launch_add_i64(int64_t* p, int64_t v, hipStream_t s);
