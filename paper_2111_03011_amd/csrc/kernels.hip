@@ -1907,6 +1907,7 @@ hipError_t launch_gemm_outer(const GemmArgs& a, hipStream_t s) {
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.config == 6) return launch_gemm_outer(a, s);
   if (a.config == 7 || a.config == 8) return launch_gemm_planes(a, s);
+  if (a.config == 9) return launch_gemm_rows(a, s);
   if (a.config == 5) {
     if (a.precision == 0 || rows_narrow_fits(a)) return launch_gemm_n8(a, s);
     GemmArgs b = a;            // the split-precision kernels have no 8-wide tile

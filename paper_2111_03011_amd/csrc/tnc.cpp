@@ -520,7 +520,8 @@ struct Compiler {
   }
 
   // GEMM tile configurations (see launch_gemm); 6 is the short-K vector kernel, 7 and 8 the
-  // plane kernels, counted as 128 x 64 tiles for split-K, whichever size a launch takes
+  // plane kernels, counted as 128 x 64 tiles for split-K, whichever size a launch takes.  9, the
+  // row products, stands outside the list: rows_ok alone gives it, and no other tile replaces it.
   static constexpr int kConfigs = 9;
 
   // read at every plan compile, so that one process can build plans both ways
@@ -608,6 +609,41 @@ struct Compiler {
       std::vector<Launch>& lst = list(Z.inv);
       lst.insert(lst.begin(), Z);
     }
+  }
+
+  // Whether k_gemm_rows takes a step: at least 256 rows of 1024 outputs (M and N of 16 and more),
+  // K of 16 to 64, in the split forms from 32 (a matrix instruction's K).  The tile kernels take 1.5
+  // to 3.6 times as long there (figures in gemm_rows.hip); with fewer rows the launch is short of
+  // workgroups, and stacked rows fill the tiles as well.
+  bool rows_ok(const TState& P, const TState& Q, int nm, int nn, int nk, int64_t rows) const {
+    if (std::getenv("TNC_GEMM_CONFIG") != nullptr) return false;
+    if (rows < 256 || rows >= (int64_t(1) << 31) || nm + nn != 10 || nm < 4 || nn < 4) return false;
+    if (nk > 6 || nk < (plan.precision == TNC_C64 ? 4 : 5)) return false;
+    return int(P.dense.size()) == nm + nk && int(Q.dense.size()) == nn + nk;
+  }
+
+  // C's rows, those that share a row of one operand side by side: the operand whose distinct rows
+  // are read less often that way, weighed by their size
+  void row_order(const TState& P, const TState& Q, const TState& C, std::vector<int32_t>& perm) {
+    const int64_t rows = C.rows();
+    auto row_of = [&](const TState& S) {
+      std::vector<int32_t> out(size_t(rows), 0);
+      for (int64_t r = 0; S.q != 0 && r < rows; ++r)
+        out[size_t(r)] = int32_t(std::lower_bound(S.keys.begin(), S.keys.end(), C.keys[size_t(r)] & S.q) - S.keys.begin());
+      return out;
+    };
+    const std::vector<int32_t> gp = row_of(P), gq = row_of(Q);
+    const double by_p = double(P.rows()) * std::ldexp(1.0, int(P.dense.size())) +
+                        double(rows) * std::ldexp(1.0, int(Q.dense.size()));
+    const double by_q = double(Q.rows()) * std::ldexp(1.0, int(Q.dense.size())) +
+                        double(rows) * std::ldexp(1.0, int(P.dense.size()));
+    const std::vector<int32_t>& g = by_p <= by_q ? gp : gq;
+    const std::vector<int32_t>& h = by_p <= by_q ? gq : gp;
+    perm.resize(size_t(rows));
+    for (int64_t r = 0; r < rows; ++r) perm[size_t(r)] = int32_t(r);
+    std::stable_sort(perm.begin(), perm.end(), [&](int32_t a, int32_t b) {
+      return g[size_t(a)] != g[size_t(b)] ? g[size_t(a)] < g[size_t(b)] : h[size_t(a)] < h[size_t(b)];
+    });
   }
 
   // Whether a step is small enough for a fused program (program.hip), and its descriptor.  X
@@ -1059,7 +1095,9 @@ struct Compiler {
     // row stacking: output rows whose M is below a tile and that share one Q row are
     // stacked along M, 128 >> nm rows per 128-row block
     std::vector<int32_t> stk, perm;
-    if (!g.fold && rows > 1 && M < 128 && Q.rows() < rows && stacking_enabled() &&
+    const bool by_rows = !g.fold && rows_ok(P, Q, nm, nn, nk, rows);
+    if (by_rows) row_order(P, Q, C, perm);
+    if (!by_rows && !g.fold && rows > 1 && M < 128 && Q.rows() < rows && stacking_enabled() &&
         double(P.elems()) < 2147483648.0) {
       // tile fill in both directions: unstacked, the better of the 64 x 32 tile and the
       // 128-row tiles (128 x 8 / 16 / 32 / 64 by N); stacked, the 128-row tile
@@ -1112,6 +1150,12 @@ struct Compiler {
       L.ntab_off = add_const(nt.data(), nt.size() * sizeof(int64_t));
     }
     choose_tiles(g, M, N, Kd, rows, !stk.empty(), planes, inv);
+    if (by_rows) {
+      g.config = 9;
+      g.k_splits = 1;
+      g.k_chunk = Kd;
+      L.perm_off = add_const(perm.data(), perm.size() * sizeof(int32_t));
+    }
     if (!stk.empty()) {
       g.k_splits = 1;   // the split-K reduce assumes C in the launch's own layout
       g.k_chunk = Kd;
@@ -1136,7 +1180,7 @@ struct Compiler {
     L.bufs = {pbuf, qbuf, C.buf};
     int part = -1;
     L.max_splits = g.k_splits;
-    L.planes = g.config >= 7;
+    L.planes = g.config == 7 || g.config == 8;
     if (g.k_splits > 1) {
       part = new_buf(uint64_t(g.k_splits) * uint64_t(rows) * uint64_t(M) * uint64_t(N) * 8, false,
                      ps);
@@ -1933,7 +1977,7 @@ int autotune(tnc_plan_s& p, uint8_t* ws, hipStream_t st, int reps) {
     std::vector<Launch>& lst = phase == 0 ? p.inv : p.dep;
     for (size_t i = 0; i < lst.size(); ++i) {
       Launch& L = lst[i];
-      if (L.kind != K_GEMM || L.fused) continue;
+      if (L.kind != K_GEMM || L.fused || L.gm.config == 9) continue;   // no other tile to choose
       const int64_t nb = (phase == 0 || L.shared) ? 1 : p.batch;
       Launch* R = (i + 1 < lst.size() && lst[i + 1].kind == K_REDUCE && lst[i + 1].b_in0 == L.b_tmp)
                       ? &lst[i + 1] : nullptr;

@@ -214,6 +214,7 @@ struct SliceSumArgs {
 // Launchers (return hipError_t of the launch).
 hipError_t launch_stream(const StreamArgs& a, hipStream_t s);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
+hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_planes(const GemmArgs& a, hipStream_t s);
 // whether configuration 5 runs a launch on the narrow-row kernel (k_gemm_rows_narrow),
 // which computes in FP32 in every form
