@@ -553,6 +553,11 @@ struct Compiler {
       g.config = 6;
     // K >= 32, at least one whole 128 x 64 tile: the 16-bit matrix cores in every form
     if (planes && M >= 128 && N >= 64) g.config = (M >= 256 && N >= 128) ? 7 : 8;
+    // 64 rows by a long contraction in the split forms: half a tile, on 64 x 64 ones (64 x 64 x 65536,
+    // 64 slices, BF16x3 1.75 -> 1.14 ms).  Complex64 keeps the FP32 kernel there: where every gate has
+    // the same angle the 30-qubit workload's last step cancels far enough that three planes are off by
+    // 1.2e-5 of its amplitudes for 1.1e-6.
+    if (planes && g.precision != 0 && M == 64 && N >= 64 && Kd >= 1024) g.config = 8;
     if (force) {
       const int f = std::min(kConfigs - 1, std::max(0, std::atoi(force)));
       if ((f != 6 || outer_ok(g, stacked)) && (f < 7 || planes)) g.config = f;
@@ -567,7 +572,7 @@ struct Compiler {
     // chip without splits, and each costs a write and a read of the whole output (1.1 of 11.3 ms
     // of the 30-qubit workload's batch in BF16x3).  The split may not follow the batch: a slice's
     // bits must not.
-    const int64_t chunk = (g.config >= 7 && !inv) ? 1024 : 256;
+    const int64_t chunk = (g.config >= 7 && !inv && M > 64) ? 1024 : 256;
     if (tiles * 4 <= target && Kd >= 2 * chunk) {
       int64_t s = 1;
       while (tiles * s * 2 <= target && Kd / (s * 2) >= chunk) s *= 2;

@@ -72,6 +72,29 @@ def test_plane_gemm_edges(case, config):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("nn,nk", [(6, 10), (8, 12), (6, 13)])
+def test_sixty_four_rows_by_a_long_contraction(nn, nk):
+    """M = 64 and K >= 1024: the 64 x 64 tile in the split forms (bounds as above), by the plan's own
+    choice and in as many splits as it makes; complex64 keeps the FP32 kernel."""
+    from paper_2111_03011_amd.contractor import Contraction
+    require_gpu()
+    rng = np.random.default_rng(nn + nk)
+    net = random_pair_network(6 + nk, nn + nk, nk, 17, _orders(rng, 6, nk, nk), _orders(rng, nn, nk, nk + 6))
+    ref = _exact(net)
+    for precision, tol in ((0, 1e-5), (1, 2.0 ** -20), (2, 2.0 ** -15)):
+        c = Contraction(net, [(0, 1)], open_qubits=list(range(net.n_qubits)), closed_bits=[0],
+                        precision=precision)
+        g = [l for l in c.launches() if l.kind == 1]
+        c.contract()
+        err = np.linalg.norm(c.amps.cpu().numpy()[0] - ref) / np.linalg.norm(ref)
+        c.close()
+        log(f"M {g[0].m} N {g[0].n} K {g[0].k} precision {precision}: config {g[0].config}, {err:.2e}")
+        if min(g[0].m, g[0].n) == 64 and g[0].m == 64:
+            assert (g[0].config == 8) == (precision != 0)
+        assert err <= tol
+
+
+@pytest.mark.gpu
 def test_plane_tiles_give_the_same_bits():
     """Both tile sizes add every output's products in one order, so a launch may take either."""
     require_gpu()
