@@ -101,7 +101,8 @@ struct PlSlot {
   }
 };
 
-template <int WM, int WN, int UM, int UN, int P, bool F16>
+// STK: rows stacked along M, 64 / 2^nm of them to a block of 64 (GemmArgs::stk with 64-row blocks).
+template <int WM, int WN, int UM, int UN, int P, bool F16, bool STK = false>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_planes(GemmArgs a) {
   constexpr int NT = WM * WN * 64, BM = WM * UM * 32, BN = WN * UN * 32;
   using SA = PlSlot<BM, NT>;
@@ -132,13 +133,31 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
   typedef const __attribute__((address_space(4))) int64_t* const_i64;
   const int row_a = SA::row(), row_b = SB::row();
   const int64_t ar = a.ga ? ((const_i32)(uintptr_t)a.ga)[r] : (a.a_rows == 1 ? 0 : int64_t(r));
-  const int64_t br = a.gb ? ((const_i32)(uintptr_t)a.gb)[r] : (a.b_rows == 1 ? 0 : int64_t(r));
-  const uint8_t* A = reinterpret_cast<const uint8_t*>(a.A + sl * a.a_slice_stride + ar * a.a_row_stride +
-                                                      ((const_i64)(uintptr_t)a.mtab)[tm * (BM >= 128 ? BM / 128 : 1)]);
+  int64_t br = a.gb ? ((const_i32)(uintptr_t)a.gb)[r] : (a.b_rows == 1 ? 0 : int64_t(r));
+  static_assert(!STK || BM == 64, "blocks of 64 stacked rows");
+  __shared__ int32_t stacked[STK ? 64 : 1];   // the block's output rows
+  int n_stacked = 0, row_m = row_a;           // rows of the block, m inside the slot's row
+  uint32_t row_elem = 0;                      // the slot's row of A
+  bool in_stk = true;
+  if constexpr (STK) {
+    const const_i32 blk = (const_i32)(uintptr_t)(a.stk + 3 * tm);
+    const int start = blk[0];
+    n_stacked = blk[1];
+    br = blk[2];
+    const int slot = row_a >> a.nm;
+    in_stk = slot < n_stacked;
+    const int32_t cr = a.perm[start + (in_stk ? slot : 0)];
+    row_m = row_a & ((1 << a.nm) - 1);
+    row_elem = uint32_t(a.ga ? a.ga[cr] : (a.a_rows == 1 ? 0 : cr)) * uint32_t(a.a_row_stride);
+    if (int(threadIdx.x) < n_stacked) stacked[threadIdx.x] = a.perm[start + threadIdx.x];
+  }
+  const uint8_t* A = reinterpret_cast<const uint8_t*>(
+      a.A + sl * a.a_slice_stride +
+      (STK ? 0 : ar * a.a_row_stride + ((const_i64)(uintptr_t)a.mtab)[tm * (BM >= 128 ? BM / 128 : 1)]));
   const uint8_t* B = reinterpret_cast<const uint8_t*>(a.B + sl * a.b_slice_stride + br * a.b_row_stride +
                                                       ((const_i64)(uintptr_t)a.ntab)[tn * (BN / 64)]);
-  const bool in_a = m0 + row_a < M, in_b = n0 + row_b < N;
-  const uint32_t voff_a = in_a ? 8u * uint32_t(scatter_u<8>(row_a, a.a_mpos, a.nm < 8 ? a.nm : 8) +
+  const bool in_a = STK ? in_stk : m0 + row_a < M, in_b = n0 + row_b < N;
+  const uint32_t voff_a = in_a ? 8u * uint32_t(row_elem + scatter_u<8>(row_m, a.a_mpos, a.nm < 8 ? a.nm : 8) +
                                                scatter_u<4>(SA::k0(), a.a_kpos, 4)) : 0u;
   const uint32_t voff_b = in_b ? 8u * uint32_t(scatter_u<8>(row_b, a.b_npos, a.nn < 8 ? a.nn : 8) +
                                                scatter_u<4>(SB::k0(), a.b_kpos, 4)) : 0u;
@@ -165,7 +184,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
 
   float sa = 1.f, sb = 1.f;
   bool scaled = false;
-  const bool full = (m0 + BM <= M) && (n0 + BN <= N);
+  const bool full = STK ? (n_stacked << a.nm) == BM && n0 + BN <= N : (m0 + BM <= M) && (n0 + BN <= N);
   const int wr_a = row_a * 64 + (((SA::k0() >> 3) ^ pl_rot(row_a)) << 4) + ((SA::k0() & 4) << 1);
   const int wr_b = row_b * 64 + (((SB::k0() >> 3) ^ pl_rot(row_b)) << 4) + ((SB::k0() & 4) << 1);
 
@@ -402,13 +421,17 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
       for (int j = 0; j < UN; ++j) {
         const float2 x = make_float2(acc[i][j][0][v], acc[i][j][1][v]);
         mx = fmaxf(mx, fmaxf(fabsf(x.x), fabsf(x.y)));
-        if (full || (mr + dm < M && nc + j * 32 < N)) pr[j * 32] = x;
+        if constexpr (STK) {
+          const int row = wm * UM * 32 + 4 * half + dm, slot = row >> a.nm;
+          if (slot < n_stacked && nc + j * 32 < N)
+            out[stacked[slot] * a.c_row_stride + (row & ((1 << a.nm) - 1)) * N + nc + j * 32] = x;
+        } else if (full || (mr + dm < M && nc + j * 32 < N)) pr[j * 32] = x;
       }
     }
   if (a.rec_c && a.k_splits == 1) amax_commit_wg(mx, sl, a.rec_c, a.rec_c_step);
 }
 
-template <int WM, int WN, int UM, int UN, int P, bool F16>
+template <int WM, int WN, int UM, int UN, int P, bool F16, bool STK = false>
 hipError_t launch_planes_t(const GemmArgs& a, hipStream_t s) {
   constexpr int BM = WM * UM * 32, BN = WN * UN * 32;
   const int64_t tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
@@ -417,7 +440,7 @@ hipError_t launch_planes_t(const GemmArgs& a, hipStream_t s) {
   const int64_t gy = zs < 65535 ? zs : 65535;
   const int64_t gz = (zs + gy - 1) / gy;
   const dim3 grid{unsigned(tiles), unsigned(gy), unsigned(gz)}, block(WM * WN * 64);
-  hipLaunchKernelGGL((k_gemm_planes<WM, WN, UM, UN, P, F16>), grid, block, 0, s, a);
+  hipLaunchKernelGGL((k_gemm_planes<WM, WN, UM, UN, P, F16, STK>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
@@ -430,7 +453,16 @@ hipError_t launch_planes_t(const GemmArgs& a, hipStream_t s) {
 // of which the small tile would leave half empty: 64 x 64 x 65536, 64 slices, BF16x3 1.75 ms on the
 // 64 x 32 tile kernel, 1.14 here, 3.7 TB/s.
 hipError_t launch_gemm_planes(const GemmArgs& a, hipStream_t s) {
-  if (a.stk || !a.ktab || a.k_chunk % kPlK) return hipErrorInvalidValue;
+  if (!a.ktab || a.k_chunk % kPlK) return hipErrorInvalidValue;
+  if (a.stk) {
+    if (a.config != 8 || a.nm > 6 || a.k_splits != 1 || a.rows != 1 || a.M % 64) return hipErrorInvalidValue;
+    switch (a.precision) {
+      case 0: return launch_planes_t<2, 2, 1, 1, 3, false, true>(a, s);
+      case 1: return launch_planes_t<2, 2, 1, 1, 2, false, true>(a, s);
+      case 3: return launch_planes_t<2, 2, 1, 1, 2, true, true>(a, s);
+    }
+    return hipErrorInvalidValue;
+  }
   const int64_t big = ((a.M + 255) / 256) * ((a.N + 127) / 128) * a.rows * a.nb * a.k_splits;
   const bool narrow = a.M <= 64 && a.precision != 0;
   const bool large = !narrow && a.config == 7 && big >= 256 && (!a.fold || a.nm >= 8);

@@ -132,6 +132,7 @@ struct Launch {
   std::vector<int> bufs;  // buffers touched (for lifetimes)
   int b_in0 = -1, b_in1 = -1, b_out = -1, b_tmp = -1;
   int64_t g0 = -1, g1 = -1;   // byte offsets of row gathers in the constants block
+  bool stacked_planes = false;           // 64-row blocks, for the plane kernel alone
   int64_t stk_off = -1, perm_off = -1;   // row-stacking tables (GEMM), same block
   int64_t ktab_off = -1, mtab_off = -1, ntab_off = -1;   // tile offset tables (GEMM), same block
   int rec_in0 = -1, rec_in1 = -1, rec_out = -1;   // scale records of the operands and result
@@ -462,7 +463,7 @@ struct Compiler {
   // output rows is then read from HBM about once and served from that XCD's L2).
   // Returns the fraction of the stacked M extent that holds real rows.
   static double stack_rows(const TState& P, const TState& Q, const TState& C, int64_t M,
-                           std::vector<int32_t>& stk, std::vector<int32_t>& perm) {
+                           std::vector<int32_t>& stk, std::vector<int32_t>& perm, int64_t block = 128) {
     const int64_t rows = C.rows();
     auto row_of = [&](const TState& S, std::vector<int32_t>& out) {
       out.assign(size_t(rows), 0);
@@ -482,7 +483,7 @@ struct Compiler {
                                                 : prow[size_t(x)] < prow[size_t(y)];
     });
     std::vector<std::array<int32_t, 3>> blocks;
-    const int64_t per = 128 / M;
+    const int64_t per = block / M;
     for (int64_t i = 0; i < rows;) {
       int64_t j = i;
       const int32_t q0 = qrow[size_t(perm[size_t(i)])];
@@ -496,7 +497,7 @@ struct Compiler {
                      });
     stk.clear();
     for (const auto& b : blocks) stk.insert(stk.end(), {b[0], b[1], b[2]});
-    return double(rows * M) / (double(stk.size() / 3) * 128.0);
+    return double(rows * M) / (double(stk.size() / 3) * double(block));
   }
 
   // Estimated fraction of the MFMA tile work that is useful, for P on the M side
@@ -625,6 +626,22 @@ struct Compiler {
     if (rows < 256 || rows >= (int64_t(1) << 31) || nm + nn != 10 || nm < 4 || nn < 4) return false;
     if (nk > 6 || nk < (plan.precision == TNC_C64 ? 4 : 5)) return false;
     return int(P.dense.size()) == nm + nk && int(Q.dense.size()) == nn + nk;
+  }
+
+  // Fill of 64-row blocks by rows of P that share a row of Q, for the plane kernel (0: not its step):
+  // P's rows below a tile, Q's at least one wide, K of 32 and more, P's slice within 32-bit offsets.
+  // From 0.4 on: 60 rows of 8 x 512, K = 256 (8 operand rows shared, fill 0.68), 64 slices, took
+  // 0.64 ms as 128 x 8 tiles of every row and take 0.33; 5000 rows of 1 x 64, K = 64 (fill 0.89), 16
+  // slices 61 us as 128-row blocks of the FP32 kernel and 44; 16 rows of 8 x 512, K = 64 (fill 1) 27
+  // and 14; 512 rows of 4 x 1024, K = 32 (fill 1), 64 slices 1.35 ms and 0.57.  An emptier block
+  // does more than twice a tile kernel's work, which is near what the 16-bit cores give.
+  double plane_fill(const TState& P, const TState& Q, const TState& C, int nm, int nn, int nk,
+                    std::vector<int32_t>& stk, std::vector<int32_t>& perm) const {
+    if (std::getenv("TNC_GEMM_CONFIG") != nullptr || !stacking_enabled()) return 0.0;
+    if (nm > 5 || nn < 6 || nk < 5 || nk > 20 || nn > 22 || Q.rows() >= C.rows()) return 0.0;
+    if (int(P.dense.size()) != nm + nk || int(Q.dense.size()) != nn + nk || nn + nk > 29) return 0.0;
+    if (double(P.elems()) >= 536870912.0 || C.rows() > (int64_t(1) << 24)) return 0.0;
+    return stack_rows(P, Q, C, int64_t(1) << nm, stk, perm, 64);
   }
 
   // C's rows, those that share a row of one operand side by side: the operand whose distinct rows
@@ -1042,6 +1059,19 @@ struct Compiler {
                                    : tile_fill(A, B, C, int(MA.size()), int(NB.size()));
       if (f_swap > 1.2 * f_keep) p_is_a = !p_is_a;
     }
+    // rows that fill 64-row blocks of the plane kernel, in either orientation
+    std::vector<int32_t> stk, perm;
+    bool stacked_planes = false;
+    if (finite && C.rows() > 1 && !rows_ok(A, B, int(MA.size()), int(NB.size()), nk, C.rows())) {
+      std::vector<int32_t> s1, p1;
+      const double f0 = plane_fill(A, B, C, int(MA.size()), int(NB.size()), nk, stk, perm);
+      const double f1 = plane_fill(B, A, C, int(NB.size()), int(MA.size()), nk, s1, p1);
+      if (std::max(f0, f1) >= 0.4) {
+        stacked_planes = true;
+        p_is_a = f0 >= f1;
+        if (!p_is_a) stk = s1, perm = p1;
+      }
+    }
     TState& P = p_is_a ? A : B;
     TState& Q = p_is_a ? B : A;
     const std::vector<int32_t>& MP = p_is_a ? MA : NB;
@@ -1099,10 +1129,13 @@ struct Compiler {
     }
     // row stacking: output rows whose M is below a tile and that share one Q row are
     // stacked along M, 128 >> nm rows per 128-row block
-    std::vector<int32_t> stk, perm;
     const bool by_rows = !g.fold && rows_ok(P, Q, nm, nn, nk, rows);
     if (by_rows) row_order(P, Q, C, perm);
-    if (!by_rows && !g.fold && rows > 1 && M < 128 && Q.rows() < rows && stacking_enabled() &&
+    if (stacked_planes) {
+      M = int64_t(stk.size() / 3) * 64;
+      rows = 1;
+    }
+    if (!by_rows && !stacked_planes && !g.fold && rows > 1 && M < 128 && Q.rows() < rows && stacking_enabled() &&
         double(P.elems()) < 2147483648.0) {
       // tile fill in both directions: unstacked, the better of the 64 x 32 tile and the
       // 128-row tiles (128 x 8 / 16 / 32 / 64 by N); stacked, the 128-row tile
@@ -1128,7 +1161,7 @@ struct Compiler {
     if (plan.precision == TNC_FP16X3) g.precision = 3;
     if (plan.precision == TNC_BF16X3) g.precision = 1;
     const bool planes =
-        planes_ok(g, !stk.empty(), M, N, int(P.dense.size()), int(Q.dense.size()), finite);
+        planes_ok(g, !stk.empty() && !stacked_planes, M, N, int(P.dense.size()), int(Q.dense.size()), finite);
     if (planes) {
       std::vector<int32_t> kt;
       for (int64_t t = 0; t < Kd / 16; ++t) {
@@ -1148,7 +1181,7 @@ struct Compiler {
         return o;
       };
       std::vector<int64_t> mt, nt;
-      for (int64_t m = 0; m < M; m += 128)
+      for (int64_t m = 0; m < M && !stacked_planes; m += 128)
         mt.push_back((g.fold ? (m >> nm) * g.fold_stride : 0) + spread(m & ((int64_t(1) << nm) - 1), g.a_mpos, nm));
       for (int64_t n = 0; n < N; n += 64) nt.push_back(spread(n, g.b_npos, nn));
       L.mtab_off = add_const(mt.data(), mt.size() * sizeof(int64_t));
@@ -1161,6 +1194,8 @@ struct Compiler {
       g.k_chunk = Kd;
       L.perm_off = add_const(perm.data(), perm.size() * sizeof(int32_t));
     }
+    if (stacked_planes) g.config = 8;
+    L.stacked_planes = stacked_planes;
     if (!stk.empty()) {
       g.k_splits = 1;   // the split-K reduce assumes C in the launch's own layout
       g.k_chunk = Kd;
@@ -1982,7 +2017,7 @@ int autotune(tnc_plan_s& p, uint8_t* ws, hipStream_t st, int reps) {
     std::vector<Launch>& lst = phase == 0 ? p.inv : p.dep;
     for (size_t i = 0; i < lst.size(); ++i) {
       Launch& L = lst[i];
-      if (L.kind != K_GEMM || L.fused || L.gm.config == 9) continue;   // no other tile to choose
+      if (L.kind != K_GEMM || L.fused || L.gm.config == 9 || L.stacked_planes) continue;   // no other tile to choose
       const int64_t nb = (phase == 0 || L.shared) ? 1 : p.batch;
       Launch* R = (i + 1 < lst.size() && lst[i + 1].kind == K_REDUCE && lst[i + 1].b_in0 == L.b_tmp)
                       ? &lst[i + 1] : nullptr;

@@ -85,7 +85,7 @@ struct GemmArgs {
   // M is then a multiple of 128 and each output row contributes 2^nm consecutive m; the
   // 128-row block b holds output rows perm[stk[3b]], ..., perm[stk[3b] + stk[3b+1] - 1]
   // and reads B row stk[3b+2].  Such a launch has rows = 1 and k_splits = 1, and A's
-  // offsets within one slice fit in 31 bits.
+  // offsets within one slice fit in 31 bits.  Configuration 8 takes blocks of 64 rows instead.
   const int32_t* stk;
   const int32_t* perm;
   // k_gemm_planes: element offsets of every 16-k tile in A and B (interleaved), of every 128th

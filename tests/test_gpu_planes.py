@@ -89,7 +89,7 @@ def test_sixty_four_rows_by_a_long_contraction(nn, nk):
         err = np.linalg.norm(c.amps.cpu().numpy()[0] - ref) / np.linalg.norm(ref)
         c.close()
         log(f"M {g[0].m} N {g[0].n} K {g[0].k} precision {precision}: config {g[0].config}, {err:.2e}")
-        if min(g[0].m, g[0].n) == 64 and g[0].m == 64:
+        if g[0].m == 64:                # 256 x 64 takes the 128 x 64 tile
             assert (g[0].config == 8) == (precision != 0)
         assert err <= tol
 
@@ -130,6 +130,35 @@ def test_plane_gemm_folded_rows(n_oa):
     err = np.linalg.norm(got - np.asarray(ref)) / np.linalg.norm(ref)
     log(f"folded rows, M 2^{n_oa}: {err:.2e}")
     assert err <= 1e-6
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("case", [(6, 3, 3, 6, 5, 60), (7, 0, 2, 7, 6, 250), (4, 5, 3, 6, 5, 37),
+                                  (7, 2, 2, 8, 9, 201), (2, 7, 7, 1, 8, 90)])
+def test_stacked_rows_on_planes(case, precision):
+    """Rows below a tile that share the other operand's row, in 64-row blocks: M from 1 to 32, ragged
+    blocks, either orientation.  Bounds as above, complex64 by its FP32 accumulation; a power of two
+    on an operand comes out as an exact factor."""
+    from paper_2111_03011_amd.contractor import Contraction
+    from tests.test_gpu_parity import _grouped_pair, _grouped_reference
+    require_gpu()
+    net, open_q, closed = _grouped_pair(*case, seed=sum(case))
+    ref = _grouped_reference(net, open_q, closed)
+    out = []
+    for scale in (1.0, 2.0 ** -60):
+        if scale != 1.0:
+            net.tensors[0] = net.tensors[0] * scale
+        c = Contraction(net, [(0, 1)], open_qubits=open_q, closed_bits=closed, precision=precision)
+        g = [l for l in c.launches() if l.kind == 1]
+        assert len(g) == 1 and g[0].config == 8 and g[0].row_mode == 2
+        c.contract()
+        out.append(c.amps.cpu().numpy().copy())
+        c.close()
+    err = np.linalg.norm(out[0] - ref) / np.linalg.norm(ref)
+    log(f"stacked rows {case} precision {precision}: {err:.2e}")
+    assert err <= {0: 2.0 ** -24 * np.sqrt(2 << case[4]), 1: 2.0 ** -20, 2: 2.0 ** -15}[precision]
+    assert np.array_equal(out[1], out[0] * 2.0 ** -60)
 
 
 def test_non_finite_leaves_keep_the_fp32_kernels():
