@@ -185,6 +185,10 @@ def kernel_family(kind: int, config: int, precision: str) -> str:
             return "k_gemm_outer"
         if config == 5 and precision == "c64":
             return "k_gemm_n8"
+        if config in (7, 8):
+            return "k_gemm_planes"
+        if config == 9:
+            return "k_gemm_rows"
         return "k_gemm" if precision == "c64" else "k_gemm_bf16x3"
     return {2: "k_stream", 3: "k_slice_leaves", 4: "k_slice_sum", 5: "k_reduce",
             6: "k_zero_u32"}.get(kind, f"kind{kind}")
@@ -211,12 +215,19 @@ def roofline(rows, precision: str, traffic):
         # algorithmic flops
         r = {"kernel": f"{dom} (complex64 on v_mfma_f32)", "bound": "mfma", "achieved": algo,
              "peak": PEAK_FP32_MFMA / 1e12, "unit": "TFLOP/s", "frac": algo / (PEAK_FP32_MFMA / 1e12)}
-    elif dom == "k_gemm_bf16x3":
+    elif dom == "k_gemm_planes" and precision == "c64":
+        # six products of 16-bit planes per algorithmic flop
+        algo = d["flops"] / (d["ms"] * 1e-3) / 1e12
+        r = {"kernel": "k_gemm_planes (complex64 on v_mfma_f32_32x32x16_bf16, 3 planes, 6 products)",
+             "bound": "mfma", "achieved": 6 * algo, "peak": PEAK_BF16_MFMA / 1e12,
+             "unit": "TFLOP/s", "frac": 6 * algo / (PEAK_BF16_MFMA / 1e12),
+             "algorithmic_tflops": algo}
+    elif dom in ("k_gemm_bf16x3", "k_gemm_planes"):
         # three products (hi*hi, hi*lo, lo*hi) per algorithmic flop; FP16 and BF16 share one
         # matrix-core peak
         algo = d["flops"] / (d["ms"] * 1e-3) / 1e12
         mf = "f16" if precision == "fp16x3" else "bf16"
-        r = {"kernel": f"k_gemm_bf16x3 (v_mfma_f32_32x32x16_{mf}, 3 products)",
+        r = {"kernel": f"{dom} (v_mfma_f32_32x32x16_{mf}, 3 products)",
              "bound": "mfma", "achieved": 3 * algo, "peak": PEAK_BF16_MFMA / 1e12,
              "unit": "TFLOP/s", "frac": 3 * algo / (PEAK_BF16_MFMA / 1e12),
              "algorithmic_tflops": algo}
@@ -236,11 +247,12 @@ def roofline(rows, precision: str, traffic):
 KIND = {1: "gemm", 2: "stream", 3: "slice_leaves", 4: "slice_sum", 5: "splitk_reduce",
         6: "scale_records"}
 TILE = {0: "128x64", 1: "128x16", 2: "64x32", 3: "128x128", 4: "128x32", 5: "128x8",
-        6: "vector", 7: "128x128w8", 8: "256x64w8"}
+        6: "vector", 7: "256x128 planes", 8: "128x64 planes", 9: "rows"}
 
 
 def step_classes(c) -> dict:
-    """Per launch of the plan (timed launches only): kind, shape, time, algorithmic
+    """Per launch of the plan (timed launches only; the steps of a fused program share its time
+    evenly): kind, shape, time, algorithmic
     TFLOP/s and GB/s of the launch (all the slices it processes); summarised by class - GEMMs above the FP32 ridge (MFMA-bound by
     their arithmetic intensity) and the rest (HBM-bound)."""
     rows = []
@@ -658,8 +670,11 @@ def traffic_json(workload: str, precision: str) -> str:
 
 def kernels_sha256():
     import hashlib
-    src = open(os.path.join(ROOT, "paper_2111_03011_amd", "csrc", "kernels.hip"), "rb").read()
-    return hashlib.sha256(src).hexdigest()
+    csrc = os.path.join(ROOT, "paper_2111_03011_amd", "csrc")
+    h = hashlib.sha256()
+    for name in sorted(f for f in os.listdir(csrc) if f.endswith((".hip", ".h"))):
+        h.update(open(os.path.join(csrc, name), "rb").read())
+    return h.hexdigest()
 
 
 def headline_mode(args) -> str:
@@ -728,7 +743,7 @@ def write_traffic(args, batch: int, fetch_csv, write_csv):
     of the dominant GEMM kernel, each counter scaled by what it reads for the plain device
     copy of known size."""
     import csv
-    name = "::k_gemm<" if args.precision == "c64" else "::k_gemm_bf16x3<"
+    name = "::k_gemm_planes<"
 
     def per_dispatch(path, counter):
         gemm, copy = {}, {}

@@ -51,8 +51,11 @@ const char* tnc_last_error(void);
  * arithmetic, however small a slice's amplitudes (a slice of a heavily sliced 53-qubit
  * network has amplitudes near 1e-39, below FP32's normal range); the FP64 slice sum
  * applies 2^E.
- *   TNC_C64     GEMM steps on the FP32 matrix cores, FP32 accumulation; operands whose
- *               largest component lies outside [2^-20, 2^21) are brought to [1, 2).
+ *   TNC_C64     FP32 products and accumulation; operands whose largest component lies
+ *               outside [2^-20, 2^21) are brought to [1, 2).  GEMM steps run on the FP32
+ *               matrix cores, or from K = 32 and one 128 x 64 tile on as the six leading
+ *               products of three BF16 planes per operand (their sum is the FP32 value
+ *               exactly), which are off by less.
  *   TNC_BF16X3  GEMM steps split every operand value x into hi = bf16(x) and
  *               lo = bf16(x - hi) and accumulate hi*hi + hi*lo + lo*hi in FP32 on the BF16
  *               matrix cores (about 16 significant bits per operand; BF16 has FP32's
@@ -213,8 +216,9 @@ tnc_status tnc_net_destroy(tnc_net net);
  * are never permuted, the GEMM reads them in their stored layouts); rows, m, n, k in
  * elements; flops and bytes algorithmic (one slice); invariant = 1 if run once per call,
  * 2 if run once per batch (head reuse, see tnc_plan_work), 0 if run per slice.  For GEMMs:
- * tile configuration (0 = 128x64, 1 = 128x16, 2 = 64x32, 3 = 128x128 complex), split-K
- * factor, and row mode (0 = one launch row per output row, 1 = rows folded into M because
+ * tile configuration (0 = 128x64, 1 = 128x16, 2 = 64x32, 3 = 128x128, 4 = 128x32, 5 = 128x8
+ * complex, 6 = short K, 7 = 256x128 and 8 = 128x64 on 16-bit planes, 9 = products of many
+ * rows), split-K factor, and row mode (0 = one launch row per output row, 1 = rows folded into M because
  * the N-side operand is shared, 2 = output rows sharing an N-side row stacked along M). */
 typedef struct {
   int32_t kind;
@@ -242,7 +246,7 @@ tnc_status tnc_plan_launch_info(tnc_plan plan, int32_t i, tnc_step_info* info);
  * slice batches (about 4096 launches per call; the other batches replay the graph);
  * tnc_plan_timing then returns, per kind (arrays of 7), the summed milliseconds, summed
  * algorithmic bytes and flops and the launch count since the last reset (synchronises on
- * the events). */
+ * the events).  Small steps that the plan runs as one launch share its time evenly. */
 tnc_status tnc_plan_set_timing(tnc_plan plan, int32_t enable);
 tnc_status tnc_plan_timing(tnc_plan plan, double* ms, double* bytes, double* flops,
                            int64_t* launches, int32_t reset);

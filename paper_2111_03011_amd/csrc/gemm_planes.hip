@@ -15,9 +15,9 @@
 // What bounds it: the matrix cores, at the rate that power allows.  Register-only loops of random
 // operands reach 2.0 PFLOP/s in BF16 but 119 TFLOP/s in FP32 on this card, so six BF16 products
 // cost 60% of one FP32 product, three 30%; with the staging beside them the clock falls to about
-// 1.6 GHz.  Measured, 64 slices of 1024 x 1024 x 1024 (start: the FP32 kernel and 128 x 64 split
-// tiles): complex64 114 -> 193 TFLOP/s, BF16x3 224 -> 320; 8192 x 1024 x 2048: 124 -> 197 and
-// 293 -> 370.  What is left is the dead time of short contractions (a tile of K = 256 spends a
+// 1.6 GHz.  Measured, 64 slices of 1024 x 1024 x 1024 (before: the FP32 kernel and 128 x 64 split
+// tiles): complex64 114 -> 197 TFLOP/s, BF16x3 224 -> 320; 8192 x 1024 x 2048: 124 -> 202 and
+// 293 -> 405.  What is left is the dead time of short contractions (a tile of K = 256 spends a
 // quarter of its time on its first loads and its output) and, for complex64, vector work (about
 // six vector instructions per matrix instruction).
 //
