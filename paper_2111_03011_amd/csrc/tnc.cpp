@@ -708,15 +708,15 @@ struct Compiler {
     p.x_elems = int32_t(X.elems());
     p.s_elems = int32_t(S.elems());
     p.flags = (nn >= 2 && (C.rows() << (nm + nn)) >= 2048) ? 8 : 0;
-    for (int64_t k = 0; k < (int64_t(1) << nk); ++k) {
-      int32_t ox = 0, os = 0;
-      for (int j = 0; j < nk; ++j)
-        if ((k >> j) & 1) {
-          ox += int32_t(1) << pos_of(X.dense, K[size_t(nk - 1 - j)]);
-          os += int32_t(1) << pos_of(S.dense, K[size_t(nk - 1 - j)]);
-        }
-      L.kx.push_back(ox);
-      L.ks.push_back(os);
+    L.kx.assign(size_t(1) << nk, 0);
+    L.ks.assign(size_t(1) << nk, 0);
+    for (int j = 0; j < nk; ++j) {
+      const int32_t bx = int32_t(1) << pos_of(X.dense, K[size_t(nk - 1 - j)]);
+      const int32_t bs = int32_t(1) << pos_of(S.dense, K[size_t(nk - 1 - j)]);
+      for (size_t k = size_t(1) << j; k < (size_t(2) << j); ++k) {   // the offsets below, and this bit
+        L.kx[k] = L.kx[k - (size_t(1) << j)] + bx;
+        L.ks[k] = L.ks[k - (size_t(1) << j)] + bs;
+      }
     }
     L.p_buf[0] = X.buf, L.p_buf[1] = S.buf, L.p_buf[2] = C.buf;
     L.p_rec[0] = X.rec, L.p_rec[1] = S.rec, L.p_rec[2] = C.rec;
