@@ -7,7 +7,7 @@
 // contiguous block: it is read with 16-byte loads while the row before is multiplied, and only when
 // it is another than the row before's; it goes to LDS as it lies, pairs of elements swizzled against
 // bank conflicts, and the matrix instructions' lanes read it at offsets that are the same for every
-// row.  Four waves hold one 256th part of M x N each.
+// row.  Each of four waves holds one 16 x 16 tile of the 1024 outputs.
 //
 // What bounds it: complex64 the FP32 matrix cores (M N K / 16 instruction cycles a row) or the write
 // of C, the split forms memory.  Measured over 64 slices of the 53-qubit share, tile kernels -> this

@@ -3,16 +3,16 @@
 // A network starts and ends in steps of a few hundred to a few ten thousand multiply-adds whose
 // launches (5 to 8 us each in a chain) cost more than their work.  The plan groups them: a launch
 // holds the trees of a forest, one workgroup contracts one tree for one slice, step by step with a
-// barrier between, its intermediates in LDS; independent small steps go to a wave each.  Measured figures stand with the plan's rule
-// (small_step in tnc.cpp).
+// barrier between, its intermediates in LDS; independent small steps go to a wave each.  Measured
+// figures stand with the plan's rule (small_step in tnc.cpp).
 //
 // What bounds it: the chain of latencies in a step.  Global memory (1 to 2 us a miss) is read ahead
 // of the first step only, all at once: the tables and the constant operands are one contiguous
 // image, operands from other launches are copied beside it.  A step then is one LDS read for its
-// descriptor (a word per lane, fields by readlane), one for
-// its records, its products, a maximum over lanes by DPP and one LDS atomic.  The larger steps are
-// bound by LDS reads, 8 bytes per operand and multiply-add, so a thread holds four outputs of one
-// row where there are enough of them; tensors stand swizzled (prog_swz) against bank conflicts.
+// descriptor (a word per lane, fields by readlane), one for its records, its products, a maximum
+// over lanes by DPP and one LDS atomic: 1.2 us for the smallest.  The larger steps are bound by LDS
+// reads, 8 bytes per operand and multiply-add, so a thread holds four outputs of one row where
+// there are enough of them; tensors stand swizzled (prog_swz) against bank conflicts.
 //
 // Arithmetic as in the stream kernels: FP32 on the vector ALUs, operands rescaled by their records.
 #include "tnc_kernels.h"
