@@ -1063,13 +1063,15 @@ struct Compiler {
     std::vector<int32_t> stk, perm;
     bool stacked_planes = false;
     if (finite && C.rows() > 1 && !rows_ok(A, B, int(MA.size()), int(NB.size()), nk, C.rows())) {
-      std::vector<int32_t> s1, p1;
-      const double f0 = plane_fill(A, B, C, int(MA.size()), int(NB.size()), nk, stk, perm);
+      // both orientations in tables of their own: the step holds one only where it is taken
+      std::vector<int32_t> s0, p0, s1, p1;
+      const double f0 = plane_fill(A, B, C, int(MA.size()), int(NB.size()), nk, s0, p0);
       const double f1 = plane_fill(B, A, C, int(NB.size()), int(MA.size()), nk, s1, p1);
       if (std::max(f0, f1) >= 0.4) {
         stacked_planes = true;
         p_is_a = f0 >= f1;
-        if (!p_is_a) stk = s1, perm = p1;
+        stk.swap(p_is_a ? s0 : s1);
+        perm.swap(p_is_a ? p0 : p1);
       }
     }
     TState& P = p_is_a ? A : B;

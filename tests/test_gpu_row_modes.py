@@ -1,0 +1,60 @@
+"""Which rows of a grouped product stack: the plan on the host, the product on the GPU.
+
+A product whose rows hold 128 and more m each has its tiles to itself, whichever operand comes
+first and however few of its rows would fill a block of the other orientation.  Tolerances
+(normwise): complex64 adds 2 K products per component, each rounded at 2^-24 of a partial sum with
+random signs, 2^-24 sqrt(2 K); the split forms drop products below 2^-15 (two BF16 planes) and
+2^-20 (two FP16 planes)."""
+
+import numpy as np
+import pytest
+
+from oracle import metrics
+from paper_2111_03011_amd import tnc
+from tests.gpu_util import log, require_gpu
+from tests.test_gpu_parity import _grouped_pair, _grouped_reference
+
+
+def plan_gemms(net, open_q, closed, precision=tnc.TNC_C64, batch=1):
+    """The GEMM launches of a two-tensor network's plan."""
+    h = tnc.tnc_net_create(0, net.n_qubits, net.ranks(), net.flat_labels(), net.flat_data(),
+                           net.out_label)
+    tnc.tnc_net_set_path(h, [(0, 1)])
+    tnc.tnc_net_set_targets(h, open_q, closed)
+    p = tnc.tnc_plan_create(h, precision, batch)
+    infos = [tnc.tnc_plan_launch_info(p, i) for i in range(tnc.tnc_plan_n_launches(p))]
+    tnc.tnc_plan_destroy(p)
+    tnc.tnc_net_destroy(h)
+    return [i for i in infos if i.kind == 1]
+
+
+# closed on A, open on A, closed on B, open on B, contracted labels, groups: few rows share a row of
+# B, so 64-row blocks of A's m would stay empty, and B (2^7 to 2^9 m) takes the M side
+LOW_FILL = [(6, 0, 6, 8, 6, 70), (6, 2, 6, 7, 6, 100), (4, 0, 4, 9, 8, 40), (5, 1, 6, 7, 5, 65)]
+
+
+@pytest.mark.parametrize("case", LOW_FILL)
+def test_whole_tiles_are_not_stacked(case):
+    n_ca, n_oa, n_cb, n_ob, nk, groups = case
+    for c in (case, (n_cb, n_ob, n_ca, n_oa, nk, groups)):
+        g, = plan_gemms(*_grouped_pair(*c, seed=sum(c)))
+        assert g.m == 1 << n_ob and g.rows == groups
+        assert g.row_mode == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("case", LOW_FILL)
+def test_whole_tiles_in_either_operand_order(case, precision):
+    require_gpu()
+    from paper_2111_03011_amd.contractor import Contraction
+    n_ca, n_oa, n_cb, n_ob, nk, groups = case
+    for c in (case, (n_cb, n_ob, n_ca, n_oa, nk, groups)):
+        net, open_q, closed = _grouped_pair(*c, seed=sum(c))
+        k = Contraction(net, [(0, 1)], open_qubits=open_q, closed_bits=closed, precision=precision)
+        assert [l.row_mode for l in k.launches() if l.kind == 1] == [0]
+        k.contract()
+        err = metrics.rel_error(k.amps.cpu().numpy(), _grouped_reference(net, open_q, closed))
+        k.close()
+        log(f"row modes {c} precision {precision}: {err:.2e}")
+        assert err <= {0: 2.0 ** -24 * np.sqrt(2 << nk), 1: 2.0 ** -20, 2: 2.0 ** -15}[precision]
