@@ -525,6 +525,8 @@ struct Compiler {
   // row products, stands outside the list: rows_ok alone gives it, and no other tile replaces it.
   static constexpr int kConfigs = 9;
 
+  static constexpr int64_t kPlaneMaxM = int64_t(1) << 23;   // launch M of a plane kernel
+
   // read at every plan compile, so that one process can build plans both ways
   static bool stacking_enabled() { return std::getenv("TNC_NO_STACK") == nullptr; }
 
@@ -538,7 +540,7 @@ struct Compiler {
   static bool planes_ok(const GemmArgs& g, bool stacked, int64_t M, int64_t N, int rank_a, int rank_b,
                         bool finite) {
     return finite && !stacked && g.nk >= 5 && g.nk <= 20 && rank_a <= 29 && rank_b <= 29 &&
-           M <= (int64_t(1) << 23) && N <= (int64_t(1) << 22) && (!g.fold || g.nm >= 7);
+           M <= kPlaneMaxM && N <= (int64_t(1) << 22) && (!g.fold || g.nm >= 7);
   }
 
   static void choose_tiles(GemmArgs& g, int64_t M, int64_t N, int64_t Kd, int64_t rows,
@@ -629,7 +631,8 @@ struct Compiler {
   }
 
   // Fill of 64-row blocks by rows of P that share a row of Q, for the plane kernel (0: not its step):
-  // P's rows below a tile, Q's at least one wide, K of 32 and more, P's slice within 32-bit offsets.
+  // P's rows below a tile, Q's at least one wide, K of 32 and more, P's slice within 32-bit offsets,
+  // the blocks within a launch's M.
   // From 0.4 on: 60 rows of 8 x 512, K = 256 (8 operand rows shared, fill 0.68), 64 slices, took
   // 0.64 ms as 128 x 8 tiles of every row and take 0.33; 5000 rows of 1 x 64, K = 64 (fill 0.89), 16
   // slices 61 us as 128-row blocks of the FP32 kernel and 44; 16 rows of 8 x 512, K = 64 (fill 1) 27
@@ -641,7 +644,8 @@ struct Compiler {
     if (nm > 5 || nn < 6 || nk < 5 || nk > 20 || nn > 22 || Q.rows() >= C.rows()) return 0.0;
     if (int(P.dense.size()) != nm + nk || int(Q.dense.size()) != nn + nk || nn + nk > 29) return 0.0;
     if (double(P.elems()) >= 536870912.0 || C.rows() > (int64_t(1) << 24)) return 0.0;
-    return stack_rows(P, Q, C, int64_t(1) << nm, stk, perm, 64);
+    const double fill = stack_rows(P, Q, C, int64_t(1) << nm, stk, perm, 64);
+    return int64_t(stk.size() / 3) * 64 <= kPlaneMaxM ? fill : 0.0;
   }
 
   // C's rows, those that share a row of one operand side by side: the operand whose distinct rows
@@ -1196,7 +1200,10 @@ struct Compiler {
       g.k_chunk = Kd;
       L.perm_off = add_const(perm.data(), perm.size() * sizeof(int32_t));
     }
-    if (stacked_planes) g.config = 8;
+    if (stacked_planes) {
+      if (!planes) fail(TNC_E_INTERNAL, "stacked rows on the plane kernel without its tables");
+      g.config = 8;
+    }
     L.stacked_planes = stacked_planes;
     if (!stk.empty()) {
       g.k_splits = 1;   // the split-K reduce assumes C in the launch's own layout

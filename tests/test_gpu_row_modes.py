@@ -42,6 +42,17 @@ def test_whole_tiles_are_not_stacked(case):
         assert g.row_mode == 0
 
 
+@pytest.mark.parametrize("case,config,mode,m", [
+    ((9, 5, 9, 6, 5, 1 << 18), 8, 2, 32),      # 2^18 rows of 32: M = 2^23, the plane kernel's largest launch
+    ((9, 5, 10, 6, 5, 266240), 2, 0, 64),      # beyond it the tile kernels, the other operand on the M side
+])
+def test_stacked_rows_up_to_the_largest_launch(case, config, mode, m):
+    net, open_q, closed = _grouped_pair(*case, seed=3)
+    for precision in (tnc.TNC_C64, tnc.TNC_BF16X3, tnc.TNC_FP16X3):
+        g, = plan_gemms(net, open_q, closed, precision)
+        assert (g.config, g.row_mode, g.rows, g.m) == (config, mode, case[5], m)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("precision", [0, 1, 2])
 @pytest.mark.parametrize("case", LOW_FILL)
