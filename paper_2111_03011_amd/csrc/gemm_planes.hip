@@ -8,9 +8,21 @@
 //
 // All accumulate in FP32.  A matrix instruction adds 16 products and rounds about twice, so two
 // planes round 6 times per 16 complex k and output; the three-plane products of 16 k first meet in
-// registers of their own and join the accumulator with one rounding.  On random 2^8 x 2^7 x 2^10
-// products complex64 errs 1.1e-7 (4.1e-7 on the FP32 matrix cores), on the full sum of the 30-qubit
-// workload 8.6e-7 (1.14e-6); the two-plane forms err as much as with interleaved parts.
+// registers of their own and join the accumulator with one rounding.
+//
+// These instructions round a little downwards where products and accumulator are alike in size:
+// normal products onto an accumulator 4 times as large err by -0.016 (+- 0.003) of 2^-24 of the
+// result on average, the FP32 instructions by less than the 0.003 that the probe resolves.  That
+// error is the same in every slice, so 1024 slices add it 32 times as fast as chance errors: sums
+// of the 30-qubit workload with 13 open qubits (128 x 64 x 16384 at the end) erred 6.0e-6 where the
+// FP32 kernel errs 1.1e-6.  So half of the K tiles are computed on -B and subtracted, which turns the
+// error's direction; the half is the middle one, for which the error's growth with the accumulator
+// cancels too.  The mean error of 2^9 x 2^8 outputs falls from 0.3 to 0.004 of the spread at most in
+// complex64 (K 32 to 4096; FP16 planes 0.18 to 0.03); those sums err 7e-7 now, FP16x3 with 12 open
+// qubits 7.2e-6 -> 1.2e-6.  It costs 8 sign changes per thread and K tile (the 30-qubit workload
+// 242.6 -> 245.1 ms, FP16x3 146.4 -> 148.6).  Over 329 sums of 16 to 30 qubits complex64 errs 0.62
+// times the FP32 kernel's on average, at most 1.02 times; the two-plane forms as much as with
+// interleaved parts where the chains are as long.
 //
 // What bounds it: the matrix cores, at the rate that power allows.  Register-only loops of random
 // operands reach 2.0 PFLOP/s in BF16 but 119 TFLOP/s in FP32 on this card, so six BF16 products
@@ -191,15 +203,20 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
   // Staging of the loaded values, two k at a time (unit e: values 2e and 2e + 1): mask and scale
   // where needed (General), split; the words of all units then go out in whole chunks.
   uint32_t wa[EA / 2][2][P], wb[EB / 2][2][P];
-  auto split_unit = [&](auto General, const float2* v, uint32_t (*w)[P], bool in, float sc) {
+  auto sign = [](float x, uint32_t flip) { return __uint_as_float(__float_as_uint(x) ^ flip); };
+  auto split_unit = [&](auto General, const float2* v, uint32_t (*w)[P], bool in, float sc, uint32_t flip) {
     float2 x = v[0], y = v[1];
     if constexpr (decltype(General)::value) {
       x = keep_if(x, in ? ~0u : 0u);
       y = keep_if(y, in ? ~0u : 0u);
     }
     if constexpr (F16 || decltype(General)::value) {
+      sc = sign(sc, flip);
       x = make_float2(x.x * sc, x.y * sc);
       y = make_float2(y.x * sc, y.y * sc);
+    } else {
+      x = make_float2(sign(x.x, flip), sign(x.y, flip));
+      y = make_float2(sign(y.x, flip), sign(y.y, flip));
     }
     split2<P, F16>(x.x, y.x, w[0]);
     split2<P, F16>(x.y, y.y, w[1]);
@@ -238,7 +255,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
   constexpr int kMfma = UM * UN * 4 * (P * (P + 1) / 2);
   // Three planes: the twelve products of an output start from zero and join the accumulator in one
   // vector addition, so that an output rounds once per 16 k at its own size.
-  auto compute3 = [&](int stage, auto&& tick) {
+  auto compute3 = [&](int stage, float one, auto&& tick) {
     static_assert(P < 3 || UN == 1, "B's fragments stay in registers");
     const uint8_t* pa = lds + stage * STAGE;
     const uint8_t* pb = pa + P * A_PL;
@@ -278,8 +295,8 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
         }
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        acc[i][0][0][v] += t0[v];
-        acc[i][0][1][v] += t1[v];
+        acc[i][0][0][v] = __builtin_fmaf(one, t0[v], acc[i][0][0][v]);
+        acc[i][0][1][v] = __builtin_fmaf(one, t1[v], acc[i][0][1][v]);
       }
     }
   };
@@ -346,13 +363,32 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     sb = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sb)));
     scaled = (sa != 1.f) || (sb != 1.f);
   }
+  // Against the matrix instructions' rounding (see the file's head): the middle half of the K tiles
+  // is computed on -B.  Three planes subtract such a tile's products; with two planes the
+  // accumulator itself changes sign where the half begins and where it ends.
+  const int turn0 = nt / 4, turn1 = nt - nt / 4 - (nt < 4 ? 1 : 0);
+  auto flip_of = [&](int t) { return t >= turn0 && t < turn1 ? 0x80000000u : 0u; };
+  auto turn = [&](int t) {
+    if constexpr (P == 2) {
+      if (t != turn0 && t != turn1) return;
+#pragma unroll
+      for (int i = 0; i < UM; ++i)
+#pragma unroll
+        for (int j = 0; j < UN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            acc[i][j][0][v] = -acc[i][j][0][v];
+            acc[i][j][1][v] = -acc[i][j][1][v];
+          }
+    }
+  };
   // Staging of one K tile as kWork items: per operand, the split of each pair of values (followed
   // by the loads of the same values of the tile after: a whole tile ahead of their use), then the
   // writes of its chunks.
   constexpr int kA = EA / 2, kB = EB / 2, kWork = kA + kB + 4 * P;
-  auto work = [&](auto General, int w, int st, bool reload) {
+  auto work = [&](auto General, int w, int st, bool reload, uint32_t flip) {
     if (w < kA) {
-      split_unit(General, ra + 2 * w, wa[w], in_a, sa);
+      split_unit(General, ra + 2 * w, wa[w], in_a, sa, 0u);
       if (reload) {
         load_a(2 * w);
         load_a(2 * w + 1);
@@ -363,7 +399,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     if (w < 2 * P) return write_a(st, w >> 1, w & 1);
     w -= 2 * P;
     if (w < kB) {
-      split_unit(General, rb + 2 * w, wb[w], in_b, sb);
+      split_unit(General, rb + 2 * w, wb[w], in_b, sb, flip);
       if (reload) {
         load_b(2 * w);
         load_b(2 * w + 1);
@@ -377,7 +413,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
   const bool general = !full || (!F16 && scaled);
   auto loop = [&](auto General) {
 #pragma unroll
-    for (int x = 0; x < kWork; ++x) work(General, x, 0, true);
+    for (int x = 0; x < kWork; ++x) work(General, x, 0, true, flip_of(0));
     offsets(2);
     __syncthreads();
     int stage = 0;
@@ -386,20 +422,23 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     constexpr int kFirst = 4, kStep = (kMfma - kFirst) / kWork >= 1 ? (kMfma - kFirst) / kWork : 1;
     constexpr int kPer = (kWork * kStep + kFirst + kMfma - 1) / kMfma;   // work items per slot
     for (int t = 0; t + 1 < nt; ++t) {
+      const uint32_t flip_next = flip_of(t + 1);
+      turn(t);
       auto each = [&](int q) {
         if (q < kFirst || (q - kFirst) % kStep) return;
 #pragma unroll
         for (int x = (q - kFirst) / kStep * kPer; x < ((q - kFirst) / kStep + 1) * kPer; ++x)
-          if (x < kWork) work(General, x, stage ^ 1, true);
+          if (x < kWork) work(General, x, stage ^ 1, true, flip_next);
         __builtin_amdgcn_sched_barrier(0);
       };
-      if constexpr (P == 3) compute3(stage, each);
+      if constexpr (P == 3) compute3(stage, sign(1.f, flip_of(t)), each);
       else compute(stage, each);
       offsets(t + 3);
       __syncthreads();
       stage ^= 1;
     }
-    if constexpr (P == 3) compute3(stage, [](int) {});
+    turn(nt - 1);
+    if constexpr (P == 3) compute3(stage, sign(1.f, flip_of(nt - 1)), [](int) {});
     else compute(stage, [](int) {});
   };
   if (general) loop(std::true_type{});

@@ -557,9 +557,8 @@ struct Compiler {
     // K >= 32, at least one whole 128 x 64 tile: the 16-bit matrix cores in every form
     if (planes && M >= 128 && N >= 64) g.config = (M >= 256 && N >= 128) ? 7 : 8;
     // 64 rows by a long contraction in the split forms: half a tile, on 64 x 64 ones (64 x 64 x 65536,
-    // 64 slices, BF16x3 1.75 -> 1.14 ms).  Complex64 keeps the FP32 kernel there: where every gate has
-    // the same angle the 30-qubit workload's last step cancels far enough that three planes are off by
-    // 1.2e-5 of its amplitudes for 1.1e-6.
+    // 64 slices, BF16x3 1.75 -> 1.14 ms).  Complex64 keeps the FP32 kernel there: its 128 x 64 plane
+    // tile would be half empty.
     if (planes && g.precision != 0 && M == 64 && N >= 64 && Kd >= 1024) g.config = 8;
     if (force) {
       const int f = std::min(kConfigs - 1, std::max(0, std::atoi(force)));
@@ -2051,9 +2050,8 @@ int autotune(tnc_plan_s& p, uint8_t* ws, hipStream_t st, int reps) {
         for (int cfg = 0; cfg < Compiler::kConfigs; ++cfg) {
           if (cfg == 5 && L.gm.precision != 0 && !narrow) continue;
           if (cfg == 6 && !Compiler::outer_ok(L.gm, L.stk_off >= 0)) continue;
-          // plane kernels only where they were planned: they round once per plane pair and 16 k,
-          // and a chain of 1024 of the 30-qubit workload's 64 x 64 x 65536 step on them took that
-          // sum's error from 1.1e-6 to 2.6e-5
+          // plane kernels only where they were planned (their tables are built there), in chains
+          // of at most 1024: a chain's rounding grows with the root of its length
           if (cfg >= 7 && !L.planes) continue;
           const int sp_min = cfg >= 7 ? int(std::min<int64_t>(L.max_splits, std::max<int64_t>(1, L.gm.K / 1024))) : 1;
           for (int sp = sp_min; sp <= (cfg == 6 ? 1 : L.max_splits); sp *= 2)

@@ -1,0 +1,61 @@
+"""The plane GEMM's rounding has no direction.
+
+The 16-bit matrix instructions round a little downwards where products and accumulator are alike in
+size (2% of 2^-24 of the result each).  An error with a direction is the same in every slice: S slices
+add S of it and only sqrt(S) of a chance error.  So the mean error of a product's components is
+compared with their spread: at most 1 / sqrt(S) of it, for complex64 with S = 1024 (a 30-qubit sum),
+for the two-plane forms with S = 64, plus 4 standard deviations of the mean itself."""
+
+import os
+
+import numpy as np
+import pytest
+
+from tests.gpu_util import log, random_pair_network, require_gpu
+from tests.test_gpu_parity import _grouped_pair, _grouped_reference
+
+
+def _check(got, ref, precision, name):
+    d = np.asarray(got - ref).reshape(-1)
+    d = np.r_[d.real, d.imag]
+    rms = np.sqrt(np.mean(d * d))
+    bound = (1.0 / 32 if precision == 0 else 1.0 / 8) + 4.0 / np.sqrt(d.size)
+    log(f"{name} precision {precision}: mean error {d.mean() / rms:+.4f} of its spread (bound {bound:.4f})")
+    assert abs(d.mean()) <= bound * rms
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("nk", [5, 6, 8, 10, 12])
+def test_products(nk, precision):
+    require_gpu()
+    from paper_2111_03011_amd.contractor import Contraction
+    net = random_pair_network(9 + nk, 8 + nk, nk, 40 + nk)
+    os.environ["TNC_GEMM_CONFIG"], os.environ["TNC_SPLITK_BLOCKS"] = "8", "1"
+    try:
+        c = Contraction(net, [(0, 1)], open_qubits=list(range(net.n_qubits)), closed_bits=[0],
+                        precision=precision)
+    finally:
+        os.environ.pop("TNC_GEMM_CONFIG")
+        os.environ.pop("TNC_SPLITK_BLOCKS")
+    assert [(l.config, l.k_splits) for l in c.launches() if l.kind == 1] == [(8, 1)]
+    c.contract()
+    got = c.amps.cpu().numpy()[0].reshape(1 << 9, -1)
+    c.close()
+    a, b = (t.astype(np.complex64).astype(np.complex128) for t in net.tensors)
+    _check(got, a.reshape(1 << 9, -1) @ b.reshape(1 << nk, -1), precision, f"K 2^{nk}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [0, 1, 2])
+def test_stacked_rows(precision):
+    require_gpu()
+    from paper_2111_03011_amd.contractor import Contraction
+    net, open_q, closed = _grouped_pair(7, 2, 2, 8, 9, 201, seed=5)
+    net.tensors = [t.astype(np.complex64).astype(np.complex128) for t in net.tensors]
+    c = Contraction(net, [(0, 1)], open_qubits=open_q, closed_bits=closed, precision=precision)
+    assert [(l.config, l.row_mode) for l in c.launches() if l.kind == 1] == [(8, 2)]
+    c.contract()
+    got = c.amps.cpu().numpy()
+    c.close()
+    _check(got, _grouped_reference(net, open_q, closed), precision, "stacked rows, K 2^9")
