@@ -88,6 +88,8 @@ __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c) {
 
 constexpr int kPlK = 16;   // complex k of one LDS stage: one matrix instruction's real K
 
+constexpr int kFold = 16;  // K tiles that one chain of FOLD spans
+
 // LDS: a plane holds one 64-byte row per m (n): real parts of 16 k, then imaginary parts, as
 // four 16-byte chunks (8 k each); chunk c of row r sits at position c ^ rot(r), so that any
 // 8 or 16 consecutive rows read (or write) one chunk without bank conflicts.
@@ -114,7 +116,12 @@ struct PlSlot {
 };
 
 // STK: rows stacked along M, 64 / 2^nm of them to a block of 64 (GemmArgs::stk with 64-row blocks).
-template <int WM, int WN, int UM, int UN, int P, bool F16, bool STK = false>
+// FOLD: the accumulators join sums of their own every kFold K tiles, each block of tiles with its
+// sign.  For FP16 planes where the tile kernels split K into chunks of 256: their error is the six
+// roundings of 16 k, and chains of 1024 err up to 1.37 times as much (28-qubit sums).  Splitting as
+// often costs a write and a read of the output per chunk: 30-qubit workload 148.6 ms with chains of
+// 1024, 176 with splits, 153.5 with sums in registers (128 x 64 tiles: the large tile has no room).
+template <int WM, int WN, int UM, int UN, int P, bool F16, bool STK = false, bool FOLD = false>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_planes(GemmArgs a) {
   constexpr int NT = WM * WN * 64, BM = WM * UM * 32, BN = WN * UN * 32;
   using SA = PlSlot<BM, NT>;
@@ -367,9 +374,34 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
   // is computed on -B.  Three planes subtract such a tile's products; with two planes the
   // accumulator itself changes sign where the half begins and where it ends.
   const int turn0 = nt / 4, turn1 = nt - nt / 4 - (nt < 4 ? 1 : 0);
-  auto flip_of = [&](int t) { return t >= turn0 && t < turn1 ? 0x80000000u : 0u; };
+  auto flip_of = [&](int t) {
+    if constexpr (FOLD) return uint32_t(t / kFold) << 31;
+    return t >= turn0 && t < turn1 ? 0x80000000u : 0u;
+  };
+  f32x16 sum[FOLD ? UM : 1][FOLD ? UN : 1][2];
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int i = 0; i < UM; ++i)
+#pragma unroll
+      for (int j = 0; j < UN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sum[i][j][0][v] = sum[i][j][1][v] = 0.f;
+  }
   auto turn = [&](int t) {
-    if constexpr (P == 2) {
+    if constexpr (FOLD) {
+      if (t % kFold || t == 0) return;
+      const float one = sign(1.f, flip_of(t - 1));   // the block of tiles before
+#pragma unroll
+      for (int i = 0; i < UM; ++i)
+#pragma unroll
+        for (int j = 0; j < UN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            sum[i][j][0][v] = __builtin_fmaf(one, acc[i][j][0][v], sum[i][j][0][v]);
+            sum[i][j][1][v] = __builtin_fmaf(one, acc[i][j][1][v], sum[i][j][1][v]);
+            acc[i][j][0][v] = acc[i][j][1][v] = 0.f;
+          }
+    } else if constexpr (P == 2) {
       if (t != turn0 && t != turn1) return;
 #pragma unroll
       for (int i = 0; i < UM; ++i)
@@ -444,6 +476,18 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
   if (general) loop(std::true_type{});
   else loop(std::false_type{});
 
+  if constexpr (FOLD) {
+    turn(nt);
+#pragma unroll
+    for (int i = 0; i < UM; ++i)
+#pragma unroll
+      for (int j = 0; j < UN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          acc[i][j][0][v] = sum[i][j][0][v];
+          acc[i][j][1][v] = sum[i][j][1][v];
+        }
+  }
   // lane: column n, 16 rows of each 32; both parts of a value leave together
   float2* out = (a.k_splits > 1) ? a.partial + (int64_t(ks) * a.rows * a.nb + zr) * M * N
                                  : a.C + sl * a.c_slice_stride + r * a.c_row_stride;
@@ -470,7 +514,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
   if (a.rec_c && a.k_splits == 1) amax_commit_wg(mx, sl, a.rec_c, a.rec_c_step);
 }
 
-template <int WM, int WN, int UM, int UN, int P, bool F16, bool STK = false>
+template <int WM, int WN, int UM, int UN, int P, bool F16, bool STK = false, bool FOLD = false>
 hipError_t launch_planes_t(const GemmArgs& a, hipStream_t s) {
   constexpr int BM = WM * UM * 32, BN = WN * UN * 32;
   const int64_t tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
@@ -479,7 +523,7 @@ hipError_t launch_planes_t(const GemmArgs& a, hipStream_t s) {
   const int64_t gy = zs < 65535 ? zs : 65535;
   const int64_t gz = (zs + gy - 1) / gy;
   const dim3 grid{unsigned(tiles), unsigned(gy), unsigned(gz)}, block(WM * WN * 64);
-  hipLaunchKernelGGL((k_gemm_planes<WM, WN, UM, UN, P, F16, STK>), grid, block, 0, s, a);
+  hipLaunchKernelGGL((k_gemm_planes<WM, WN, UM, UN, P, F16, STK, FOLD>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
@@ -511,6 +555,8 @@ hipError_t launch_gemm_planes(const GemmArgs& a, hipStream_t s) {
       if (large) return launch_planes_t<4, 2, 2, 2, 2, false>(a, s);
       return narrow ? launch_planes_t<2, 2, 1, 1, 2, false>(a, s) : launch_planes_t<2, 2, 2, 1, 2, false>(a, s);
     case 3:
+      if (a.k_fold && !narrow && a.k_chunk > kFold * kPlK)
+        return launch_planes_t<2, 2, 2, 1, 2, true, false, true>(a, s);
       if (large) return launch_planes_t<4, 2, 2, 2, 2, true>(a, s);
       return narrow ? launch_planes_t<2, 2, 1, 1, 2, true>(a, s) : launch_planes_t<2, 2, 2, 1, 2, true>(a, s);
   }

@@ -572,9 +572,12 @@ struct Compiler {
     g.k_chunk = Kd;
     // Chunks of at least 256; of 1024 for a plane kernel's step of every slice: a batch fills the
     // chip without splits, and each costs a write and a read of the whole output (1.1 of 11.3 ms
-    // of the 30-qubit workload's batch in BF16x3).  The split may not follow the batch: a slice's
-    // bits must not.
-    const int64_t chunk = (g.config >= 7 && !inv && M > 64) ? 1024 : 256;
+    // of the 30-qubit workload's batch in BF16x3).  FP16x3 closes its chains every 256 k inside
+    // the kernel (FOLD in gemm_planes.hip).  The split may not follow the batch: a slice's bits must
+    // not.
+    const bool longer = g.config >= 7 && !inv && M > 64;
+    const int64_t chunk = longer ? 1024 : 256;
+    g.k_fold = longer && g.precision == 3 && tiles * 4 <= target && Kd > 256;
     if (tiles * 4 <= target && Kd >= 2 * chunk) {
       int64_t s = 1;
       while (tiles * s * 2 <= target && Kd / (s * 2) >= chunk) s *= 2;

@@ -93,6 +93,7 @@ struct GemmArgs {
   const int32_t* ktab;
   const int64_t* mtab;
   const int64_t* ntab;
+  int k_fold;                 // FP16 planes: products of every 256 k join sums of their own
   int group_m;                // tiles are numbered in groups of group_m tile rows (L2 reuse)
   // scale records of A, B and C (see kRecWords); with k_splits > 1 the reduction folds
   // C's largest component in, the GEMM writes its exponent

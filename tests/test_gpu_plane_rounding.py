@@ -59,3 +59,32 @@ def test_stacked_rows(precision):
     got = c.amps.cpu().numpy()
     c.close()
     _check(got, _grouped_reference(net, open_q, closed), precision, "stacked rows, K 2^9")
+
+
+@pytest.mark.gpu
+def test_fp16_chains_are_as_short_as_the_tile_kernels():
+    """FP16 planes and the 128 x 64 tile kernel round as often per product, so a sliced step errs as
+    much on either (1.05 for chance: 2^14 components) when their chains are as long: planes in chunks
+    of 1024 close theirs every 256 k."""
+    require_gpu()
+    from paper_2111_03011_amd import tnc
+    from paper_2111_03011_amd.contractor import Contraction
+    net = random_pair_network(7 + 14, 6 + 14, 14, 8)
+    a, b = (t.astype(np.complex64).astype(np.complex128) for t in net.tensors)
+    ref = a.reshape(1 << 7, -1) @ b.reshape(1 << 14, -1)
+    err = []
+    for force in ("0", None):
+        if force:
+            os.environ["TNC_GEMM_CONFIG"] = force
+        try:
+            c = Contraction(net, [(0, 1)], sliced_labels=[0], slice_ids=[0, 1], max_batch_slices=2,
+                            open_qubits=list(range(net.n_qubits)), closed_bits=[0], precision=tnc.TNC_FP16X3)
+        finally:
+            os.environ.pop("TNC_GEMM_CONFIG", None)
+        g, = [l for l in c.launches() if l.kind == 1]
+        assert (g.config, g.k, g.k_splits) == (0, 1 << 13, 32) if force else (8, 1 << 13, 8)
+        c.contract()
+        err.append(np.linalg.norm(c.amps.cpu().numpy()[0] - ref.reshape(-1)) / np.linalg.norm(ref))
+        c.close()
+    log(f"FP16x3, K 2^13: tile kernel {err[0]:.2e}, planes {err[1]:.2e}")
+    assert err[1] <= 1.05 * err[0]
