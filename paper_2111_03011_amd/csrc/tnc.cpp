@@ -650,6 +650,41 @@ struct Compiler {
     return int64_t(stk.size() / 3) * 64 <= kPlaneMaxM ? fill : 0.0;
   }
 
+  // whether C's rows fold into P's m: Q's row is shared by all, P's rows line up with C's
+  static bool folds(const TState& P, const TState& Q, const TState& C, int nm) {
+    return C.rows() > 1 && Q.rows() == 1 && P.q == C.q && nm >= 7;
+  }
+
+  // Row stacking of the tile kernels: output rows whose M is below a tile and that share one Q row
+  // are stacked along M, 128 >> nm rows per 128-row block, where that fills the tiles better.
+  static bool stacks(const TState& P, const TState& Q, const TState& C, int nm, int nn, std::vector<int32_t>& stk,
+                     std::vector<int32_t>& perm) {
+    const int64_t M = int64_t(1) << nm, N = int64_t(1) << nn;
+    if (nm >= 7 || C.rows() <= 1 || Q.rows() >= C.rows() || !stacking_enabled() || double(P.elems()) >= 2147483648.0)
+      return false;
+    // tile fill in both directions: unstacked, the better of the 64 x 32 tile and the
+    // 128-row tiles (128 x 8 / 16 / 32 / 64 by N); stacked, the 128-row tile
+    const double nd = double(N);
+    const double n128 = std::min(1.0, nd / (N <= 8 ? 8.0 : N <= 16 ? 16.0 : N <= 32 ? 32.0 : 64.0));
+    const double fill_plain = std::max(std::min(1.0, double(M) / 64.0) * std::min(1.0, nd / 32.0),
+                                       std::min(1.0, double(M) / 128.0) * n128);
+    if (stack_rows(P, Q, C, M, stk, perm) * n128 > 1.25 * fill_plain) return true;
+    stk.clear();
+    perm.clear();
+    return false;
+  }
+
+  // whether the tile kernels split a step's K
+  static bool tiles_split(const TState& P, const TState& Q, const TState& C, int nm, int nn, int nk, bool inv) {
+    std::vector<int32_t> stk, perm;
+    if (nk < 9 || stacks(P, Q, C, nm, nn, stk, perm)) return false;
+    GemmArgs g{};
+    g.nk = nk;
+    const int64_t fold = folds(P, Q, C, nm) ? C.rows() : 1;
+    choose_tiles(g, fold << nm, int64_t(1) << nn, int64_t(1) << nk, C.rows() / fold, false, false, inv);
+    return g.k_splits > 1;
+  }
+
   // C's rows, those that share a row of one operand side by side: the operand whose distinct rows
   // are read less often that way, weighed by their size
   void row_order(const TState& P, const TState& Q, const TState& C, std::vector<int32_t>& perm) {
@@ -1065,7 +1100,9 @@ struct Compiler {
                                    : tile_fill(A, B, C, int(MA.size()), int(NB.size()));
       if (f_swap > 1.2 * f_keep) p_is_a = !p_is_a;
     }
-    // rows that fill 64-row blocks of the plane kernel, in either orientation
+    // Rows that fill 64-row blocks of the plane kernel, in either orientation; not where the tile
+    // kernels split a long K, which blocks (whose K stays whole) leave to few workgroups: 8 rows of
+    // 8 x 256, K = 2048, one slice 50 us split and 113 in blocks, K = 8192 57 and 422.
     std::vector<int32_t> stk, perm;
     bool stacked_planes = false;
     if (finite && C.rows() > 1 && !rows_ok(A, B, int(MA.size()), int(NB.size()), nk, C.rows())) {
@@ -1073,7 +1110,9 @@ struct Compiler {
       std::vector<int32_t> s0, p0, s1, p1;
       const double f0 = plane_fill(A, B, C, int(MA.size()), int(NB.size()), nk, s0, p0);
       const double f1 = plane_fill(B, A, C, int(NB.size()), int(MA.size()), nk, s1, p1);
-      if (std::max(f0, f1) >= 0.4) {
+      const bool split = p_is_a ? tiles_split(A, B, C, int(MA.size()), int(NB.size()), nk, inv)
+                                : tiles_split(B, A, C, int(NB.size()), int(MA.size()), nk, inv);
+      if (std::max(f0, f1) >= 0.4 && !split) {
         stacked_planes = true;
         p_is_a = f0 >= f1;
         stk.swap(p_is_a ? s0 : s1);
@@ -1126,7 +1165,7 @@ struct Compiler {
     // (a tile never straddles two rows: the per-row M is at least the largest tile)
     const int64_t rows_c = rows, m_c = M;
     int64_t c_row_stride = M * N;
-    if (rows > 1 && Q.rows() == 1 && P.q == C.q && M >= 128) {
+    if (folds(P, Q, C, nm)) {
       g.fold = 1;
       g.fold_stride = g.a_row_stride;
       M *= rows;
@@ -1135,30 +1174,15 @@ struct Compiler {
       g.a_row_stride = 0;
       c_row_stride = M * N;
     }
-    // row stacking: output rows whose M is below a tile and that share one Q row are
-    // stacked along M, 128 >> nm rows per 128-row block
     const bool by_rows = !g.fold && rows_ok(P, Q, nm, nn, nk, rows);
     if (by_rows) row_order(P, Q, C, perm);
     if (stacked_planes) {
       M = int64_t(stk.size() / 3) * 64;
       rows = 1;
     }
-    if (!by_rows && !stacked_planes && !g.fold && rows > 1 && M < 128 && Q.rows() < rows && stacking_enabled() &&
-        double(P.elems()) < 2147483648.0) {
-      // tile fill in both directions: unstacked, the better of the 64 x 32 tile and the
-      // 128-row tiles (128 x 8 / 16 / 32 / 64 by N); stacked, the 128-row tile
-      const double nd = double(N);
-      const double n128 = std::min(1.0, nd / (N <= 8 ? 8.0 : N <= 16 ? 16.0 : N <= 32 ? 32.0 : 64.0));
-      const double fill_plain = std::max(std::min(1.0, double(M) / 64.0) * std::min(1.0, nd / 32.0),
-                                         std::min(1.0, double(M) / 128.0) * n128);
-      const double fill_stacked = stack_rows(P, Q, C, M, stk, perm) * n128;
-      if (fill_stacked > 1.25 * fill_plain) {
-        M = int64_t(stk.size() / 3) * 128;
-        rows = 1;
-      } else {
-        stk.clear();
-        perm.clear();
-      }
+    if (!by_rows && !stacked_planes && stacks(P, Q, C, nm, nn, stk, perm)) {
+      M = int64_t(stk.size() / 3) * 128;
+      rows = 1;
     }
     g.M = M;
     g.N = N;

@@ -47,10 +47,28 @@ def test_whole_tiles_are_not_stacked(case):
     ((9, 5, 10, 6, 5, 266240), 2, 0, 64),      # beyond it the tile kernels, the other operand on the M side
 ])
 def test_stacked_rows_up_to_the_largest_launch(case, config, mode, m):
-    net, open_q, closed = _grouped_pair(*case, seed=3)
+    net, open_q, _ = _grouped_pair(*case[:5], 2, seed=3)
+    closed_q = [q for q in range(net.n_qubits) if q not in open_q]
+    rows = np.arange(case[5], dtype=np.uint64)
+    closed = np.zeros(case[5], np.uint64)
+    for b, q in enumerate(closed_q[::-1]):
+        closed |= ((rows >> np.uint64(b)) & np.uint64(1)) << np.uint64(net.n_qubits - 1 - q)
     for precision in (tnc.TNC_C64, tnc.TNC_BF16X3, tnc.TNC_FP16X3):
         g, = plan_gemms(net, open_q, closed, precision)
         assert (g.config, g.row_mode, g.rows, g.m) == (config, mode, case[5], m)
+
+
+@pytest.mark.parametrize("case,stacked", [
+    ((3, 3, 0, 8, 8, 8), True), ((3, 3, 0, 8, 9, 8), False), ((1, 5, 0, 6, 13, 2), False),
+    ((6, 5, 2, 6, 11, 40), True), ((9, 5, 4, 8, 9, 1000), True),
+])
+def test_a_long_contraction_keeps_its_splits(case, stacked):
+    """Rows stack on the plane kernel, which leaves K whole, only where the tile kernels leave it
+    whole too: K below 512 or enough tiles."""
+    for precision in (tnc.TNC_C64, tnc.TNC_BF16X3, tnc.TNC_FP16X3):
+        g, = plan_gemms(*_grouped_pair(*case, seed=4), precision)
+        assert (g.config == 8 and g.row_mode == 2) == stacked
+        assert (g.k_splits > 1) == (not stacked)
 
 
 @pytest.mark.gpu
