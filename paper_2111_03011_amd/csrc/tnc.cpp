@@ -544,7 +544,7 @@ struct Compiler {
   }
 
   static void choose_tiles(GemmArgs& g, int64_t M, int64_t N, int64_t Kd, int64_t rows,
-                           bool stacked, bool planes, bool inv) {
+                           bool stacked, bool planes, bool inv, int64_t slices) {
     static const int group = std::getenv("TNC_GEMM_GROUP") ? std::atoi(std::getenv("TNC_GEMM_GROUP")) : 4;
     g.group_m = group;
     const char* force = std::getenv("TNC_GEMM_CONFIG");
@@ -570,12 +570,15 @@ struct Compiler {
     const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN) * rows;
     g.k_splits = 1;
     g.k_chunk = Kd;
-    // Chunks of at least 256; of 1024 for a plane kernel's step of every slice: a batch fills the
-    // chip without splits, and each costs a write and a read of the whole output (1.1 of 11.3 ms
-    // of the 30-qubit workload's batch in BF16x3).  FP16x3 closes its chains every 256 k inside
-    // the kernel (FOLD in gemm_planes.hip).  The split may not follow the batch: a slice's bits must
-    // not.
-    const bool longer = g.config >= 7 && !inv && M > 64;
+    // Chunks of at least 256; of 1024 for a plane kernel's step of every slice whose slices together
+    // fill the chip that way (one workgroup for each of the 256 CUs): more splits cost a write and a
+    // read of the whole output each, fewer leave CUs idle.  Chunks of 1024 against 256, us a slice:
+    // 1024 x 1024 x 1024, 16 slices BF16x3 59 and 75; 512 x 256 x 1024, 16 slices complex64 14.8 and
+    // 19.1, 4 slices 35 and 22; 128 x 64 x 16384, 16 slices 50 and 51, one slice 149 and 89.  A plan
+    // of many slices run a few at a time pays the difference: the split may not follow the batch, a
+    // slice's bits must not.  FP16x3 closes its chains every 256 k inside the kernel (FOLD in
+    // gemm_planes.hip).
+    const bool longer = g.config >= 7 && !inv && M > 64 && tiles * std::max<int64_t>(1, Kd / 1024) * slices >= 256;
     const int64_t chunk = longer ? 1024 : 256;
     g.k_fold = longer && g.precision == 3 && tiles * 4 <= target && Kd > 256;
     if (tiles * 4 <= target && Kd >= 2 * chunk) {
@@ -681,7 +684,7 @@ struct Compiler {
     GemmArgs g{};
     g.nk = nk;
     const int64_t fold = folds(P, Q, C, nm) ? C.rows() : 1;
-    choose_tiles(g, fold << nm, int64_t(1) << nn, int64_t(1) << nk, C.rows() / fold, false, false, inv);
+    choose_tiles(g, fold << nm, int64_t(1) << nn, int64_t(1) << nk, C.rows() / fold, false, false, inv, 1);
     return g.k_splits > 1;
   }
 
@@ -1219,7 +1222,7 @@ struct Compiler {
       L.mtab_off = add_const(mt.data(), mt.size() * sizeof(int64_t));
       L.ntab_off = add_const(nt.data(), nt.size() * sizeof(int64_t));
     }
-    choose_tiles(g, M, N, Kd, rows, !stk.empty(), planes, inv);
+    choose_tiles(g, M, N, Kd, rows, !stk.empty(), planes, inv, plan.n_slices());
     if (by_rows) {
       g.config = 9;
       g.k_splits = 1;
