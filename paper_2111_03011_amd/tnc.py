@@ -165,9 +165,9 @@ def tnc_net_set_slices_wide(net: int, sliced_labels, slice_ids) -> None:
 
 def set_slices_any(net: int, sliced_labels, slice_ids) -> None:
     if len(sliced_labels) <= 63:
-        # an array of the ids' own type goes through as it is (one int at a time took 0.5 of the
-        # 0.6 ms in which a request of 4096 slices is described); others are checked value by value
-        if not (isinstance(slice_ids, np.ndarray) and slice_ids.dtype == np.uint64):
+        # a plain array of ids of their own type goes through as it is (one int at a time took 0.5 of
+        # the 0.6 ms in which a request of 4096 slices is described); others are read value by value
+        if not (type(slice_ids) is np.ndarray and slice_ids.ndim == 1 and slice_ids.dtype == np.uint64):
             slice_ids = np.asarray([int(x) for x in slice_ids], np.uint64)
         tnc_net_set_slices(net, sliced_labels, slice_ids)
     else:

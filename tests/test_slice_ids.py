@@ -32,3 +32,13 @@ def test_ids_out_of_range_are_refused(ids):
     with pytest.raises((tnc.TncError, OverflowError)):
         tnc.set_slices_any(h, [0, 1], ids)
     tnc.tnc_net_destroy(h)
+
+
+@pytest.mark.parametrize("ids", [np.array([[0, 1], [2, 3]], np.uint64), np.matrix([0, 1], dtype=np.uint64),
+                                 np.array(1, np.uint64), np.ma.array([0, 1], mask=[0, 1], dtype=np.uint64)])
+def test_other_arrays_are_read_value_by_value(ids):
+    """Rows of a matrix, an array without a dimension and a masked value are not slice ids."""
+    h = _net()
+    with pytest.raises((TypeError, ValueError, np.ma.MaskError)):
+        tnc.set_slices_any(h, [0, 1], ids)
+    tnc.tnc_net_destroy(h)
