@@ -180,6 +180,8 @@ def timed_steps(c, w, args, steps: int, warmup: int, tag: str):
 
 def kernel_family(kind: int, config: int, precision: str) -> str:
     """Name of the HIP kernel (template family) a launch of the plan runs."""
+    if config == 10:
+        return "k_program"
     if kind == 1:
         if config == 6:
             return "k_gemm_outer"
@@ -247,7 +249,7 @@ def roofline(rows, precision: str, traffic):
 KIND = {1: "gemm", 2: "stream", 3: "slice_leaves", 4: "slice_sum", 5: "splitk_reduce",
         6: "scale_records"}
 TILE = {0: "128x64", 1: "128x16", 2: "64x32", 3: "128x128", 4: "128x32", 5: "128x8",
-        6: "vector", 7: "256x128 planes", 8: "128x64 planes", 9: "rows"}
+        6: "vector", 7: "planes", 8: "planes", 9: "rows", 10: "program"}
 
 
 def step_classes(c) -> dict:
@@ -271,7 +273,7 @@ def step_classes(c) -> dict:
         rows.append({"i": i, "kind": KIND.get(s.kind, str(s.kind)), "kind_id": s.kind,
                      "config": s.config, "flops": s.flops, "bytes": s.bytes, "inv": s.invariant,
                      "rows": s.rows, "m": s.m, "n": s.n, "k": s.k,
-                     "tile": TILE.get(s.config, "-") if s.kind == 1 else "-",
+                     "tile": TILE.get(s.config, "-") if s.kind == 1 or s.config == 10 else "-",
                      "splits": s.k_splits, "row_mode": s.row_mode, "ms": t, "count": n,
                      "tflops": s.flops / (t * 1e-3) / 1e12 if t > 0 else 0.0,
                      "gbs": s.bytes / (t * 1e-3) / 1e9 if t > 0 else 0.0,

@@ -215,11 +215,14 @@ tnc_status tnc_net_destroy(tnc_net net);
  * call for slice-invariant tensors, once per batch for the others) (0 is reserved: operands
  * are never permuted, the GEMM reads them in their stored layouts); rows, m, n, k in
  * elements; flops and bytes algorithmic (one slice); invariant = 1 if run once per call,
- * 2 if run once per batch (head reuse, see tnc_plan_work), 0 if run per slice.  For GEMMs:
+ * 2 if run once per batch (head reuse, see tnc_plan_work), 0 if run per slice.  config = 10
+ * marks a small GEMM or stream that runs in a fused program with others.  For other GEMMs:
  * tile configuration (0 = 128x64, 1 = 128x16, 2 = 64x32, 3 = 128x128, 4 = 128x32, 5 = 128x8
- * complex, 6 = short K, 7 = 256x128 and 8 = 128x64 on 16-bit planes, 9 = products of many
- * rows), split-K factor, and row mode (0 = one launch row per output row, 1 = rows folded into M because
- * the N-side operand is shared, 2 = output rows sharing an N-side row stacked along M). */
+ * complex, 6 = short K, 7 and 8 = 16-bit planes, 9 = products of many rows), split-K factor,
+ * and row mode (0 = one launch row per output row, 1 = rows folded into M because the N-side
+ * operand is shared, 2 = output rows sharing an N-side row stacked along M).  Configuration 7
+ * takes 256x128 tiles where they give every compute unit one (two planes; three planes, TNC_C64,
+ * always 128x64), 8 takes 128x64, or 64x64 up to 64 rows of two planes and for stacked rows. */
 typedef struct {
   int32_t kind;
   int32_t invariant;

@@ -154,6 +154,8 @@ struct Launch {
   int p_buf[3] = {-1, -1, -1}, p_rec[3] = {-1, -1, -1};
 };
 
+constexpr int kProgramConfig = 10;   // reported for steps that a program runs
+
 // What one launch of the device executes: a step, or a fused program of small steps (trees of a
 // forest, in step order).  The lists of launches stay in path order.
 struct Unit {
@@ -581,6 +583,7 @@ struct Compiler {
     const bool longer = g.config >= 7 && !inv && M > 64 && tiles * std::max<int64_t>(1, Kd / 1024) * slices >= 256;
     const int64_t chunk = longer ? 1024 : 256;
     g.k_fold = longer && g.precision == 3 && tiles * 4 <= target && Kd > 256;
+    if (g.k_fold && !force) g.config = 8;
     if (tiles * 4 <= target && Kd >= 2 * chunk) {
       int64_t s = 1;
       while (tiles * s * 2 <= target && Kd / (s * 2) >= chunk) s *= 2;
@@ -2768,6 +2771,7 @@ tnc_status tnc_plan_launch_info(tnc_plan p, int32_t i, tnc_step_info* info) {
       info->k_splits = L.gm.k_splits;
       info->row_mode = L.stk_off >= 0 ? 2 : (L.gm.fold ? 1 : 0);
     }
+    if (L.fused) info->config = kProgramConfig;
   });
 }
 

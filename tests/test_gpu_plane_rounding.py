@@ -82,7 +82,7 @@ def test_fp16_chains_are_as_short_as_the_tile_kernels():
         finally:
             os.environ.pop("TNC_GEMM_CONFIG", None)
         g, = [l for l in c.launches() if l.kind == 1]
-        assert (g.config, g.k, g.k_splits) == (0, 1 << 10, 4) if force else (7, 1 << 10, 1)
+        assert (g.config, g.k, g.k_splits) == (0, 1 << 10, 4) if force else (8, 1 << 10, 1)
         c.contract()
         err.append(np.linalg.norm(c.amps.cpu().numpy()[0] - ref.reshape(-1)) / np.linalg.norm(ref))
         c.close()
