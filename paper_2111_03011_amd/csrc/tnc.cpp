@@ -2086,6 +2086,8 @@ int autotune(tnc_plan_s& p, uint8_t* ws, hipStream_t st, int reps) {
           // plane kernels only where they were planned (their tables are built there), in chains
           // of at most 1024: a chain's rounding grows with the root of its length
           if (cfg >= 7 && !L.planes) continue;
+          // one tile size, one kernel
+          if ((cfg == 7 || cfg == 8) && cfg != best.first && (L.gm.precision == 0 || L.gm.k_fold)) continue;
           const int sp_min = cfg >= 7 ? int(std::min<int64_t>(L.max_splits, std::max<int64_t>(1, L.gm.K / 1024))) : 1;
           for (int sp = sp_min; sp <= (cfg == 6 ? 1 : L.max_splits); sp *= 2)
             if ((sp == 1 || L.gm.K / sp >= 256) && std::make_pair(cfg, sp) != best)

@@ -3,11 +3,12 @@
 import os
 
 import numpy as np
+import pytest
 
 import synth
 from paper_2111_03011_amd import tnc
 from paper_2111_03011_amd.workload import make_workload
-from tests.gpu_util import random_pair_network
+from tests.gpu_util import log, random_pair_network, require_gpu
 
 
 def _infos(net, path, open_q, closed, precision=tnc.TNC_C64, slices=None, batch=1):
@@ -50,3 +51,23 @@ def test_fp16_sums_in_registers_are_the_small_tile():
         g, = [i for i in _infos(net, [(0, 1)], list(range(18)), [0], precision,
                                 ([0, 1, 2], np.arange(8, dtype=np.uint64)), 8) if i.kind == 1]
         assert (g.config, g.k, g.k_splits) == (config, 1 << 10, 1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nm,nn,planned,twin", [(8, 7, 7, 8), (7, 6, 8, 7)])
+def test_autotuner_leaves_a_twin_kernel_alone(nm, nn, planned, twin):
+    """Complex64 planes have one tile size, so the other configuration is not a choice."""
+    require_gpu()
+    from paper_2111_03011_amd.contractor import Contraction
+    net = random_pair_network(nm + 10, nn + 10, 10, 3)
+    c = Contraction(net, [(0, 1)], open_qubits=list(range(net.n_qubits)), closed_bits=[0])
+    assert [l.config for l in c.launches() if l.kind == 1] == [planned]
+    changed = c.autotune(reps=2)
+    tuned = [l.config for l in c.launches() if l.kind == 1]
+    log(f"2^{nm} x 2^{nn} x 2^10: planned {planned}, tuned {tuned}, {changed} changed")
+    assert tuned != [twin]
+    c.contract()
+    ref = net.tensors[0].reshape(1 << nm, -1) @ net.tensors[1].reshape(1 << 10, -1)
+    err = np.linalg.norm(c.amps.cpu().numpy()[0] - ref.reshape(-1)) / np.linalg.norm(ref)
+    c.close()
+    assert err <= 1e-5
