@@ -1594,7 +1594,10 @@ __global__ __launch_bounds__(kThreads) void k_sample_one_group(
 // One draw from each of many groups: per workgroup `gw` groups' weights are loaded together
 // (coalesced) into LDS, then a thread per group adds its weights in mu order and searches the sums.
 // Bound by HBM once the chip is full; one thread reading its group from memory left most of every
-// line unused: 16384 groups of 64 (16.8 MB) took 20.3 us, and take 7.4, 2.3 TB/s.
+// line unused: 16384 groups of 64 (16.8 MB) took 20.3 us, and take 7.4, 2.3 TB/s.  Groups up to what
+// LDS holds with four workgroups to a CU (4096 weights, 32 KiB); from 1024 weights on a workgroup has
+// one group and one lane adds it, and the loads still decide: whole calls on 4096 groups of 1024 335
+// -> 121 us, of 4096 1300 -> 402, on 2 groups of 4096 470 -> 74; groups of 1 to 8 as before.
 constexpr int kGroupTile = 1024, kGroupMaxL = 4096;
 
 __global__ __launch_bounds__(kThreads) void k_sample_groups_lds(
@@ -2023,9 +2026,10 @@ hipError_t launch_sample(const double* amps, int64_t L, int n_open, const uint64
                          double* cum, uint64_t* out, hipStream_t s) {
   if (L == 1) {
     const int64_t l = int64_t(1) << n_open;
-    // one workgroup up to 4096 draws and as many weights, which its LDS holds: the draws then take
-    // a few us, a launch of their own that searches global memory 7 and the gap before it
-    if (l <= 2 * kCumTile && n_samples <= 4096) {
+    // one workgroup up to 4096 weights, which its LDS holds, and 2048 draws (two a thread): of 4096
+    // weights 100 draws take 70 us in one launch, 2000 75 and 4096 81; with a launch of their own that
+    // searches global memory 4097 take 75 and 8192 77 (of 256 weights 30, 33, 36 and 34, 35)
+    if (l <= 2 * kCumTile && n_samples <= 2 * kCumThreads) {
       hipLaunchKernelGGL(k_cumsum_one_group<true>, dim3(1), dim3(kCumThreads), 0, s, amps, l, cum, closed,
                          n_open, open_q, n, seed, n_samples, out);
     } else {

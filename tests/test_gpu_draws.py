@@ -44,3 +44,9 @@ def test_draws_match_oracle(case):
     want = sampling.bitstrings(sampling.sample(amps, 11, draws), w.closed_bits, w.open_qubits,
                                w.net.n_qubits)
     assert np.array_equal(got, want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("draws", [2047, 2048, 2049])
+def test_draws_on_both_sides_of_one_workgroup(draws):
+    test_draws_match_oracle((12, 1, draws))
