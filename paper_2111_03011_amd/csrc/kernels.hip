@@ -246,7 +246,7 @@ constexpr int kKLevels = 4;
 
 template <int BM, int BN, int BK, bool A_MFAST, bool B_NFAST, bool LDS_TAB, int NT = kThreads>
 struct GemmTile {
-  static constexpr int LBM = (BM == 256) ? 8 : (BM == 128) ? 7 : (BM == 64 ? 6 : 5);
+  static constexpr int LBM = (BM == 128) ? 7 : (BM == 64 ? 6 : 5);
   static constexpr int LBN = (BN == 128) ? 7 : (BN == 64 ? 6 : (BN == 32 ? 5 : (BN == 16 ? 4 : 3)));
   static constexpr int LBK = (BK == 16) ? 4 : (BK == 32 ? 5 : 3);
   static constexpr int A_LD = BM * BK / NT;

@@ -907,10 +907,8 @@ struct Compiler {
         int buf, rec, elems;
       };
       std::vector<Op> ops;            // from outside the tree
-      size_t n_k = 0;
       for (int j : tree) {
         const Launch& L = lst[size_t(j)];
-        n_k += L.kx.size();
         for (int o = 0; o < 2; ++o)
           if (!made.count(L.p_buf[o]))
             ops.push_back(Op{L.p_buf[o], L.p_rec[o], o ? L.ps.s_elems : L.ps.x_elems});
