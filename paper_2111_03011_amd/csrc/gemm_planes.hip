@@ -1,8 +1,10 @@
 // Complex GEMM on the 16-bit matrix cores, operands split into planes while they are staged.
 //
-//   TNC_C64      three BF16 planes: x = hi + mid + lo exactly (8 significant bits each), six
-//                products (every pair whose planes' orders add up to at most two); the dropped
-//                ones are below 2^-25 of |a||b|, under FP32's own rounding of a product
+//   TNC_C64      three BF16 planes: x = hi + mid + lo exactly (8 significant bits each; from
+//                2^-102 on, below which lo and then mid leave BF16's normal range: operands are
+//                scaled, so that is 2^-82 of the largest component or less), six products (every
+//                pair whose planes' orders add up to at most two); the dropped ones are below
+//                2^-26 of |a||b|, under FP32's own rounding of a product
 //   TNC_BF16X3   two BF16 planes, hi*hi + hi*lo + lo*hi
 //   TNC_FP16X3   two FP16 planes of operands scaled by a power of two, the same products
 //
@@ -19,7 +21,7 @@
 // error's direction; the half is the middle one, for which the error's growth with the accumulator
 // cancels too.  The mean error of 2^9 x 2^8 outputs falls from 0.3 to 0.004 of the spread at most in
 // complex64 (K 32 to 4096; FP16 planes 0.18 to 0.03); those sums err 7e-7 now, FP16x3 with 12 open
-// qubits 7.2e-6 -> 1.2e-6.  It costs 8 sign changes per thread and K tile (the 30-qubit workload
+// qubits 7.2e-6 -> 1.2e-6 (1.0e-6 with FOLD, below).  It costs 8 sign changes per thread and K tile (the 30-qubit workload
 // 242.6 -> 245.1 ms, FP16x3 146.4 -> 148.6).  Over 329 sums of 16 to 30 qubits complex64 errs 0.62
 // times the FP32 kernel's on average, at most 1.02 times; the two-plane forms as much as with
 // interleaved parts where the chains are as long.
@@ -28,8 +30,8 @@
 // operands reach 2.0 PFLOP/s in BF16 but 119 TFLOP/s in FP32 on this card, so six BF16 products
 // cost 60% of one FP32 product, three 30%; with the staging beside them the clock falls to about
 // 1.6 GHz.  Measured, 64 slices of 1024 x 1024 x 1024 (before: the FP32 kernel and 128 x 64 split
-// tiles): complex64 114 -> 197 TFLOP/s, BF16x3 224 -> 320; 8192 x 1024 x 2048: 124 -> 202 and
-// 293 -> 405.  What is left is the dead time of short contractions (a tile of K = 256 spends a
+// tiles): complex64 114 -> 203 TFLOP/s, BF16x3 224 -> 405, FP16x3 330; 8192 x 1024 x 2048: 124 -> 209
+// and 293 -> 426.  What is left is the dead time of short contractions (a tile of K = 256 spends a
 // quarter of its time on its first loads and its output) and, for complex64, vector work (about
 // six vector instructions per matrix instruction).
 //

@@ -627,7 +627,8 @@ struct Compiler {
     }
   }
 
-  // Whether k_gemm_rows takes a step: at least 256 rows of 1024 outputs (M and N of 16 and more),
+  // Whether k_gemm_rows takes a step: at least 256 rows of 1024 outputs (each of the kernel's four
+  // waves holds one 16 x 16 tile; other sizes are not built, M and N are 16 and more),
   // K of 16 to 64, in the split forms from 32 (a matrix instruction's K).  The tile kernels take 1.5
   // to 3.6 times as long there (figures in gemm_rows.hip); with fewer rows the launch is short of
   // workgroups, and stacked rows fill the tiles as well.
@@ -644,8 +645,10 @@ struct Compiler {
   // From 0.4 on: 60 rows of 8 x 512, K = 256 (8 operand rows shared, fill 0.68), 64 slices, took
   // 0.64 ms as 128 x 8 tiles of every row and take 0.33; 5000 rows of 1 x 64, K = 64 (fill 0.89), 16
   // slices 61 us as 128-row blocks of the FP32 kernel and 44; 16 rows of 8 x 512, K = 64 (fill 1) 27
-  // and 14; 512 rows of 4 x 1024, K = 32 (fill 1), 64 slices 1.35 ms and 0.57.  An emptier block
-  // does more than twice a tile kernel's work, which is near what the 16-bit cores give.
+  // and 14; 512 rows of 4 x 1024, K = 32 (fill 1), 64 slices 1.35 ms and 0.57.  At the line itself
+  // (fill 0.42 and 0.44, K = 32 and 256, 16 slices, 32 steps in complex64 and BF16x3) blocks take
+  // 0.61 to 0.81 of the tile kernels' time on average, at most 1.02; an emptier block does more than
+  // twice a tile kernel's work, which is near what the 16-bit cores give.
   double plane_fill(const TState& P, const TState& Q, const TState& C, int nm, int nn, int nk,
                     std::vector<int32_t>& stk, std::vector<int32_t>& perm) const {
     if (std::getenv("TNC_GEMM_CONFIG") != nullptr || !stacking_enabled()) return 0.0;

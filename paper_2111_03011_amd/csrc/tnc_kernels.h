@@ -79,7 +79,8 @@ struct GemmArgs {
   int64_t k_chunk;
   float2* partial;
   int config;                 // tile configuration id
-  int precision;              // 0: complex64 on FP32 MFMA; 1: BF16 hi+lo split in the kernel;
+  int precision;              // 0: complex64 (FP32 MFMA, three BF16 planes in configurations 7
+                              // and 8); 1: BF16 hi+lo split in the kernel;
                               // 3: FP16 hi+lo of operands scaled to [2^13, 2^14) per slice
   // Row stacking (stk != nullptr): output rows that share one B row are stacked along M.
   // M is then a multiple of 128 and each output row contributes 2^nm consecutive m; the
